@@ -89,8 +89,11 @@ enum {
  *     per step).
  * coeffs: HOST float[steps][3] (a_t, b_t, c_t), or NULL for Muon's retuned
  *   quintic (3.4445, -4.7750, 2.0315) at every step (Sec. 3 setup).
- * Precision: the f32 entry points compute in float32 (MFMA fp32, float32
- *   accumulation); their sketch products accumulate in float64 and the
+ * Precision: the f32 entry points compute in float32 (float32 data and
+ *   accumulation; the filter's products take each float32 operand as a pair of
+ *   fp16 values, hi + lo, in three fp16 MFMAs, or run on the fp32 MFMA when
+ *   the coefficient table lets the iterate leave [2^-6, 4] in norm); their
+ *   sketch products accumulate in float64 and the
  *   residual M - U_k S_k V_k^T is formed in float64 (rounded once). The bf16
  *   entry points take bfloat16 input and output (uint16_t bit patterns). Their
  *   front end runs at float32 precision: the sketch products take each float32
@@ -252,7 +255,8 @@ int sd_sketch_host(int batch, int s, int rp, uint64_t seed, float* out);
  *     with nothing deflated, P = X (I + g(X / theta)) / 2 symmetrized
  *     (eq:baseline_projection);
  *   - Qwarm <- CholeskyQR(Zt) (the basis for the next call).
- * Everything is float32 (MFMA fp32), small factorizations float64.
+ * Everything is float32 (the filter's products as for the f32 Muon entry
+ * points above), small factorizations float64.
  * Tracked bases up to 32 columns keep their K x K problems in one
  * work-group's LDS; wider ones (up to 512, the paper's K = ceil(0.05 n) at
  * its SDP sizes) take float64 panel products, a one-work-group Cholesky
@@ -264,8 +268,8 @@ int sd_sketch_host(int batch, int s, int rp, uint64_t seed, float* out);
  * (Qwarm unused, may be NULL).
  */
 /* Arithmetic of the sign filter's products (the paper's SDP experiments run
- * the filter in fp16, App. E): SD_PREC_F32 computes them in float32 (fp32
- * MFMA); SD_PREC_F16 rounds every product operand to fp16 (round to nearest
+ * the filter in fp16, App. E): SD_PREC_F32 computes them in float32 (operands
+ * as fp16 pairs); SD_PREC_F16 rounds every product operand to fp16 (round to nearest
  * even) and accumulates in float32 (fp16 MFMA), the restore product R g
  * included, whose operands are fp16(R / theta) and fp16(g) (scaled back by
  * theta). The iterate, the Gram and b A + c A^2 are stored in float32 either

@@ -42,6 +42,29 @@ __device__ __forceinline__ uint32_t pack_h2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, f16x2_t));
 }
 
+// Tag of fp32 product operands split into fp16 pairs: 2^e x = hi + lo with
+// hi = fp16(2^e x) and lo = fp16(2^e x - hi). The pair keeps 23 bits of x, or
+// an absolute 2^-25 (scaled) where lo is subnormal; a product of two such
+// operands takes hi hi + hi lo + lo hi on the fp16 MFMA. (32 bits, like the
+// data it stands for.)
+struct s16_t {
+  uint32_t bits;
+};
+// Four floats (bits) scaled by 2^e and split.
+__device__ __forceinline__ void split4(const u32x4_t& x, int e, u32x2_t& hi, u32x2_t& lo) {
+  float v[4], d[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_ldexpf(__uint_as_float(x[i]), e);
+  const f16x2_t h0 = __builtin_convertvector((f32x2_t{v[0], v[1]}), f16x2_t);
+  const f16x2_t h1 = __builtin_convertvector((f32x2_t{v[2], v[3]}), f16x2_t);
+  d[0] = v[0] - (float)h0[0];
+  d[1] = v[1] - (float)h0[1];
+  d[2] = v[2] - (float)h1[0];
+  d[3] = v[3] - (float)h1[1];
+  hi = u32x2_t{__builtin_bit_cast(uint32_t, h0), __builtin_bit_cast(uint32_t, h1)};
+  lo = u32x2_t{pack_h2(d[0], d[1]), pack_h2(d[2], d[3])};
+}
+
 // ------------------------------------------------- iterate state ----------
 // The bf16 iterate is stored as hi = bf16(x) plus one residual byte: the OCP
 // float8 e4m3 ("fn") code of (x - hi) 2^16, clamped to +-448 and rounded to

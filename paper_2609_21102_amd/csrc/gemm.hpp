@@ -13,6 +13,9 @@
 // padded to 144 bytes; two stages are double buffered.
 //   bf16: v_mfma_f32_32x32x16_bf16, one 16-byte chunk per lane per MFMA.
 //   fp32: v_mfma_f32_32x32x2f32, one 16-byte chunk feeds four MFMAs.
+//   split fp32 (s16_t): the fp32 values are split into fp16 pairs while they
+//     are staged (32 hi, then 32 lo values per LDS row); three
+//     v_mfma_f32_32x32x16_f16 per 16 values of k. Memory holds fp32 throughout.
 // Lane l (h = l / 32) reads chunk 2 g + h of its row for chunk-pair g, so A
 // and B always agree on which k each lane supplies.
 //
@@ -38,6 +41,7 @@ template <typename T> struct GemmK;
 template <> struct GemmK<bf16_t> { static constexpr int BK = 64; };
 template <> struct GemmK<f16_t> { static constexpr int BK = 64; };
 template <> struct GemmK<float> { static constexpr int BK = 32; };
+template <> struct GemmK<s16_t> { static constexpr int BK = 32; };
 
 struct GemmShape {
   int M, N, K;
@@ -56,6 +60,11 @@ struct GemmShape {
   float* part = nullptr;
   long long part_cap = 0;
   int tail0 = 0, pieces = 0;
+  // Split products (s16_t): the operands are scaled by 2^ea and 2^eb on the
+  // way into LDS. With dev_exp, A is scaled by 2^(ea - ex) instead, ex the
+  // binary exponent of *dev_exp (0 when that is zero or not finite).
+  int ea = 0, eb = 0;
+  const float* dev_exp = nullptr;
 };
 
 enum { EMIT_FULL = 0, EMIT_SYM_OFF = 1, EMIT_SYM_DIAG = 2 };
@@ -631,11 +640,7 @@ struct GemmCfg {
   static constexpr int NT = 64 * NWM * NWN;
 };
 using CfgTile128 = GemmCfg<2, 2, 2, 2>;          // 128 x 128, 256 threads
-using CfgTile256 = GemmCfg<2, 4, 4, 2>;          // 256 x 256, 512 threads
-// Single-stage tiles with registers capped for two work-groups per CU, so
-// that one's epilogue (HBM traffic) overlaps the other's main loop.
-using CfgTile256x128s = GemmCfg<2, 2, 4, 2, 1, 2>;   // 256 x 128, 256 threads
-using CfgTile128s = GemmCfg<2, 2, 2, 2, 1, 2>;       // 128 x 128, 256 threads
+using CfgTile64 = GemmCfg<2, 2, 1, 1>;           // 64 x 64, 256 threads
 // Direct-to-LDS kernel: 128 x 128, two-stage ring, two work-groups per CU.
 using CfgDma128 = GemmCfg<2, 2, 2, 2, 2, 2>;
 using CfgDma256 = GemmCfg<2, 4, 4, 2, 2, 2>;   // 256 x 256, eight waves, one work-group per CU
@@ -673,13 +678,44 @@ struct RowStager {
       }
     }
   }
-  __device__ __forceinline__ void store(char* lds) const {
+  __device__ __forceinline__ void store(char* lds, int = 0) const {
     const int t = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       const int id = t + NT * u, row = id >> 3, ch = id & 7;
       if constexpr (CONV) st16(lds + row * G_ROWB + ch * 16, pack8<T>(r[2 * u], r[2 * u + 1]));
       else st16(lds + row * G_ROWB + ch * 16, r[u]);
+    }
+  }
+};
+
+// The same tile of fp32 data split into fp16 pairs (s16_t): an LDS row holds
+// the 32 hi values, then the 32 lo values. Eight floats per unit.
+template <int ROWS, int NT>
+struct RowStager<ROWS, NT, s16_t, float> {
+  static constexpr int UNITS = ROWS * 4 / NT;
+  u32x4_t r[2 * UNITS];
+  __device__ __forceinline__ void load(const float* base, int ld, int row0, int k0) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const int id = t + NT * u, row = id >> 2, ch = id & 3;
+      const float* p = base + (long long)(row0 + row) * ld + k0 + ch * 8;
+      r[2 * u] = ld16(p);
+      r[2 * u + 1] = ld16(p + 4);
+    }
+  }
+  __device__ __forceinline__ void store(char* lds, int ex) const {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const int id = t + NT * u, row = id >> 2, ch = id & 3;
+      u32x2_t h0, l0, h1, l1;
+      split4(r[2 * u], ex, h0, l0);
+      split4(r[2 * u + 1], ex, h1, l1);
+      char* p = lds + row * G_ROWB + ch * 16;
+      st16(p, u32x4_t{h0[0], h0[1], h1[0], h1[1]});
+      st16(p + 64, u32x4_t{l0[0], l0[1], l1[0], l1[1]});
     }
   }
 };
@@ -743,30 +779,44 @@ struct NNStager<COLS, NT, bf16_t, S> {       // 64 x COLS tile, bf16 LDS
   }
 };
 
-template <int COLS, int NT>
-struct NNStager<COLS, NT, float, float> {    // 32 x COLS tile, fp32 LDS
+// 32 x COLS tile of fp32 data; fp32 LDS rows (T = float), or split into fp16
+// pairs (T = s16_t: 32 hi values, then 32 lo values).
+template <int COLS, int NT, typename T>
+struct NNStager<COLS, NT, T, float> {
+  static_assert(sizeof(T) == 4, "fp32 data");
   static constexpr int KB = 8;
-  static constexpr int UNITS = KB * (COLS / 4) / NT;
+  static constexpr int TOTAL = KB * (COLS / 4), UNITS = (TOTAL + NT - 1) / NT;
+  static constexpr bool WHOLE = TOTAL % NT == 0;   // else the last unit's threads past TOTAL idle
   u32x4_t r[UNITS * 4];
   __device__ __forceinline__ void load(const float* base, int ld, int k0, int n0) {
     const int t = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       const int id = t + NT * u, kb = id % KB, nb = id / KB;
+      if (!WHOLE && id >= TOTAL) continue;
       const float* p = base + (long long)(k0 + 4 * kb) * ld + n0 + 4 * nb;
 #pragma unroll
       for (int i = 0; i < 4; ++i) r[u * 4 + i] = ld16(p + i * (long long)ld);
     }
   }
-  __device__ __forceinline__ void store(char* lds) const {
+  __device__ __forceinline__ void store(char* lds, int ex = 0) const {
     const int t = threadIdx.x;
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       const int id = t + NT * u, kb = id % KB, nb = id / KB;
+      if (!WHOLE && id >= TOTAL) continue;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const u32x4_t w = {r[u * 4][j], r[u * 4 + 1][j], r[u * 4 + 2][j], r[u * 4 + 3][j]};
-        st16(lds + (4 * nb + j) * G_ROWB + 16 * kb, w);
+        char* p = lds + (4 * nb + j) * G_ROWB;
+        if constexpr (std::is_same<T, s16_t>::value) {
+          u32x2_t hi, lo;
+          split4(w, ex, hi, lo);
+          *reinterpret_cast<u32x2_t*>(p + 8 * kb) = hi;
+          *reinterpret_cast<u32x2_t*>(p + 64 + 8 * kb) = lo;
+        } else {
+          st16(p + 16 * kb, w);
+        }
       }
     }
   }
@@ -777,6 +827,37 @@ template <typename T, int WM, int WN>
 __device__ __forceinline__ void tile_mma(const char* la, const char* lb, f32x16_t (&acc)[WM][WN], int wm,
                                          int wn, int lane) {
   const int r32 = lane & 31, h = lane >> 5;
+  if constexpr (std::is_same<T, s16_t>::value) {
+    // per 16 values of k: the small products lo hi and hi lo, then hi hi
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      u32x4_t ah[WM], al[WM], bh[WN], bl[WN];
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        const char* p = la + (wm * WM * 32 + i * 32 + r32) * G_ROWB + (2 * g + h) * 16;
+        ah[i] = ld16(p);
+        al[i] = ld16(p + 64);
+      }
+#pragma unroll
+      for (int i = 0; i < WN; ++i) {
+        const char* p = lb + (wn * WN * 32 + i * 32 + r32) * G_ROWB + (2 * g + h) * 16;
+        bh[i] = ld16(p);
+        bl[i] = ld16(p + 64);
+      }
+#pragma unroll
+      for (int mi = 0; mi < WM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < WN; ++ni) acc[mi][ni] = mfma32_f16(al[mi], bh[ni], acc[mi][ni]);
+#pragma unroll
+      for (int mi = 0; mi < WM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < WN; ++ni) acc[mi][ni] = mfma32_f16(ah[mi], bl[ni], acc[mi][ni]);
+#pragma unroll
+      for (int mi = 0; mi < WM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < WN; ++ni) acc[mi][ni] = mfma32_f16(ah[mi], bh[ni], acc[mi][ni]);
+    }
+  } else {
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     u32x4_t a[WM], b[WN];
@@ -796,6 +877,14 @@ __device__ __forceinline__ void tile_mma(const char* la, const char* lb, f32x16_
         }
       }
   }
+  }
+}
+
+// Exponent of operand A's scale (GemmShape::dev_exp).
+__device__ __forceinline__ int split_exp(const GemmShape& sh) {
+  if (!sh.dev_exp) return sh.ea;
+  const float d = *sh.dev_exp;
+  return sh.ea - (d > 0.f && d < __builtin_inff() ? __builtin_amdgcn_frexp_expf(d) : 0);
 }
 
 // Upper-triangle tile index -> (tm, tn) with tm <= tn.
@@ -924,11 +1013,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, Cfg::NT), amdgpu_waves_
       else sb.load(Bb, sh.ldb, n0, k0);
     };
     const int nk = sh.K / BK;
+    const int ea = split_exp(sh), eb = sh.eb;
     const int kb = tail ? piece * nk / sh.pieces : 0, ke = tail ? (piece + 1) * nk / sh.pieces : nk;
     load_tiles(kb * BK);
     if constexpr (Cfg::STAGES == 2) {
-      sa.store(lds);
-      sb.store(lds + TA);
+      sa.store(lds, ea);
+      sb.store(lds + TA, eb);
       __syncthreads();
       for (int kt = kb; kt < ke; ++kt) {
         const int cur = (kt - kb) & 1;
@@ -937,15 +1027,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, Cfg::NT), amdgpu_waves_
         tile_mma<T, WM, WN>(lds + cur * STAGE, lds + cur * STAGE + TA, acc, wm, wn, lane);
         if (more) {
           char* nxt = lds + (cur ^ 1) * STAGE;
-          sa.store(nxt);
-          sb.store(nxt + TA);
+          sa.store(nxt, ea);
+          sb.store(nxt + TA, eb);
         }
         __syncthreads();
       }
     } else {
       for (int kt = kb; kt < ke; ++kt) {
-        sa.store(lds);
-        sb.store(lds + TA);
+        sa.store(lds, ea);
+        sb.store(lds + TA, eb);
         __syncthreads();
         if (kt + 1 < ke) load_tiles((kt + 1) * BK);
         tile_mma<T, WM, WN>(lds, lds + TA, acc, wm, wn, lane);
@@ -967,6 +1057,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, Cfg::NT), amdgpu_waves_
   }
 
   const int mode = SYM ? (tm == tn ? EMIT_SYM_DIAG : EMIT_SYM_OFF) : EMIT_FULL;
+  const int eo = std::is_same<T, s16_t>::value ? -(split_exp(sh) + sh.eb) : 0;   // back to the operands' scale
 #pragma unroll
   for (int mi = 0; mi < WM; ++mi)
 #pragma unroll
@@ -975,6 +1066,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, Cfg::NT), amdgpu_waves_
       for (int i = 0; i < 4; ++i) {
         float v[4] = {acc[mi][ni][4 * i], acc[mi][ni][4 * i + 1], acc[mi][ni][4 * i + 2],
                       acc[mi][ni][4 * i + 3]};
+        if constexpr (std::is_same<T, s16_t>::value) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = __builtin_amdgcn_ldexpf(v[j], eo);
+        }
         const int r0 = m0 + wm * WM * 32 + mi * 32 + 8 * i + 4 * h;
         const int c = n0 + wn * WN * 32 + ni * 32 + r32;
         if constexpr (PRE) epi.apply(b, r0, c, v, mode, &px[(mi * WN + ni) * 16 + 4 * i]);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -140,6 +141,74 @@ inline dim3 grid1(long long n, int block) { return dim3((unsigned)((n + block - 
 
 inline void fill(float* p, long long n, float v, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(fill_kernel, grid1(n, 256), dim3(256), 0, st, p, n, v);
+}
+
+// ------------------------------------------------ split fp32 products -----
+// Scales of a filter's split fp32 products (s16_t). fp16 pairs hold 23 bits
+// only inside fp16's exponent range, so each operand is scaled by a power of
+// two taken from a bound on its norm, which the coefficient table gives:
+// ||X_t|| <= rho_t with rho_0 the start's nominal norm and rho_{t+1} the
+// largest |p_t(x)| on [0, rho_t]. The scales leave a factor of 4 or more above
+// the bound (a cubic start up to sqrt(5), the edge of its convergence, fits).
+// ok is false for tables that let the iterate grow past 4 or shrink below
+// 2^-6 (or hold NaN): those products stay on the fp32 MFMA, which has no
+// range to respect and takes 2.2 times as long (n = 4096).
+struct SplitScales {
+  bool ok = true;
+  std::vector<int> x, a, b;   // exponents for X_t, A_t = X_t X_t^T and B_t = b A + c A^2
+};
+template <typename Coef>
+inline SplitScales split_scales(int steps, float rho0, Coef coef) {
+  SplitScales r;
+  double rho = rho0;
+  for (int t = 0; t <= steps; ++t) {
+    if (!(rho >= 0x1p-6 && rho <= 4.0)) {
+      r.ok = false;
+      return r;
+    }
+    const int c = (int)std::ceil(std::log2(rho));
+    r.x.push_back(14 - c);
+    r.a.push_back(11 - 2 * c);
+    if (t == steps) break;
+    float ca, cb, cc;
+    coef(t, ca, cb, cc);
+    double pm = 0.0, qm = 0.0;
+    for (int i = 0; i <= 256; ++i) {
+      const double x = rho * i / 256.0, q = x * x * (cb + cc * x * x), v = std::fabs(x * (ca + q));
+      if (!(v <= pm)) pm = v;   // also takes a NaN
+      qm = std::fmax(qm, std::fabs(q));
+    }
+    if (!(qm <= 256.0)) {
+      r.ok = false;
+      return r;
+    }
+    r.b.push_back(qm >= 0x1p-20 ? 13 - (int)std::ceil(std::log2(qm)) : 13);
+    rho = 1.01 * pm;
+  }
+  return r;
+}
+
+// fp32 product of the filters on split fp16 pairs (scales 2^ea, 2^eb) or, with
+// split = false, on the fp32 MFMA. The fp32 MFMA bound these products (n =
+// 4096 symmetric: 543 us, 0.78 of its peak); three fp16 MFMAs per 16 values of
+// k take 250 us (825 TFLOP/s executed) and, with a shorter chain of float32
+// sums, round no worse. Grids of at most 192 tiles of 128 x 128 (three
+// quarters of the CUs; a long K loop on few work-groups) take 64 x 64 tiles:
+// 1 x 256 x 256 398 -> 308 us per call, 3 x 515 x 301 506 -> 377 us, PSD n =
+// 2048 2299 -> 2070 us; at 384 tiles they lose (6 x 512 x 2048: 665 with, 708
+// us without this bound).
+template <bool B_NN, bool SYM, typename Epi>
+void gemm_f32(const float* A, const float* B, GemmShape g, const Epi& e, bool split, int ea, int eb,
+              hipStream_t st) {
+  if (!split) {
+    launch_gemm<CfgTile128, float, B_NN, SYM>(A, B, g, e, st);
+    return;
+  }
+  g.ea = ea;
+  g.eb = eb;
+  const long long tm = g.M / 128, tn = g.N / 128, blocks = (SYM ? tm * (tm + 1) / 2 : tm * tn) * g.batch;
+  if (blocks <= 192) launch_gemm<CfgTile64, s16_t, B_NN, SYM>(A, B, g, e, st);
+  else launch_gemm<CfgTile128, s16_t, B_NN, SYM>(A, B, g, e, st);
 }
 
 // ----------------------------------------------------------- dispatch -----

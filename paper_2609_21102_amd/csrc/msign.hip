@@ -125,23 +125,18 @@ static void make_plan(MsignPlan& p, int batch, int m, int n, int k, int steps, i
 }
 
 // Iterate update X <- a X + B X on 128 x 128 tiles; the epilogue's X reads
-// are issued before the main loop. bf16 path: operand tiles move into a
-// two-stage LDS ring by direct-to-LDS loads, two work-groups per CU; fp32
-// path: register-staged tiles.
-template <typename T, typename SX, typename Epi>
-static void update_gemm(const MsignPlan& p, const T* bm, const SX* xop, const GemmShape& g, const Epi& eu,
-                        hipStream_t st) {
-  (void)p;
-  if constexpr (sizeof(T) == 2) launch_gemm_dma<CfgDma128, true, false>(bm, xop, g, eu, st);
-  else launch_gemm<CfgTile128, T, true, false>(bm, xop, g, eu, st);
+// are issued before the main loop. Operand tiles move into a two-stage LDS
+// ring by direct-to-LDS loads, two work-groups per CU.
+template <typename Epi>
+static void update_gemm(const bf16_t* bm, const bf16_t* xop, const GemmShape& g, const Epi& eu, hipStream_t st) {
+  launch_gemm_dma<CfgDma128, true, false>(bm, xop, g, eu, st);
 }
 
 // Symmetric products (Gram and A^2) on 128 x 128 tiles, upper-triangle tiles
-// only; direct-to-LDS loads on the bf16 path.
-template <typename T, typename Epi>
-static void sym_gemm(const T* a, const GemmShape& g, const Epi& e, hipStream_t st) {
-  if constexpr (sizeof(T) == 2) launch_gemm_dma<CfgDma128, false, true>(a, a, g, e, st);
-  else launch_gemm<CfgTile128, T, false, true>(a, a, g, e, st);
+// only; direct-to-LDS loads.
+template <typename Epi>
+static void sym_gemm(const bf16_t* a, const GemmShape& g, const Epi& e, hipStream_t st) {
+  launch_gemm_dma<CfgDma128, false, true>(a, a, g, e, st);
 }
 
 // Residual floor rho of the padded start, relative to ||X||_F: the rounding
@@ -334,10 +329,20 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
     if constexpr (BF) return reinterpret_cast<const T*>(cur16);
     else return reinterpret_cast<const T*>(cur);
   };
+  const auto coef = [&](int t, float& a, float& b, float& c) {
+    a = coeffs ? coeffs[3 * t] : 3.4445f;
+    b = coeffs ? coeffs[3 * t + 1] : -4.7750f;
+    c = coeffs ? coeffs[3 * t + 2] : 2.0315f;
+  };
+  // fp32 path: products on split fp16 pairs where the table bounds the
+  // iterates; ||X0|| is at most 1 (residual) next to 1 / gamma (padded head)
+  const SplitScales sc = BF ? SplitScales{}
+                            : split_scales(p.steps, p.k > 0 && !p.explicit_restore ? std::max(1.f, 1.f / o.gamma) : 1.f,
+                                           coef);
+  const auto at = [&](const std::vector<int>& v, int t) { return sc.ok ? v[t] : 0; };
   for (int t = 0; t < p.steps; ++t) {
-    const float a = coeffs ? coeffs[3 * t] : 3.4445f;
-    const float b = coeffs ? coeffs[3 * t + 1] : -4.7750f;
-    const float c = coeffs ? coeffs[3 * t + 2] : 2.0315f;
+    float a, b, c;
+    coef(t, a, b, c);
     GemmShape g1{p.s_pad, p.s_pad, p.l_pad, p.l_pad, p.l_pad, sl, sl, B};
     EpiGram eg{};
     eg.stride = ss;
@@ -360,11 +365,11 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       ProfScope ps(SD_STAGE_NS_GRAM, st);
       if constexpr (BF) {
         if (stream_outputs((long long)B * ss * ((eg.out32 ? 4 : 0) + (eg.out16 ? 2 : 0))))
-          sym_gemm<T>(xop(), g1, eg, st);
+          sym_gemm(xop(), g1, eg, st);
         else
-          sym_gemm<T>(xop(), g1, cached_stores(eg), st);
+          sym_gemm(xop(), g1, cached_stores(eg), st);
       } else {
-        sym_gemm<T>(xop(), g1, eg, st);
+        gemm_f32<false, true>(cur, cur, g1, eg, sc.ok, at(sc.x, t), at(sc.x, t), st);
       }
     }
     if (c != 0.f) {
@@ -373,10 +378,10 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       const T* aop = BF ? reinterpret_cast<const T*>(p.a16) : reinterpret_cast<const T*>(p.a32);
       ProfScope ps(SD_STAGE_NS_POLY, st);
       if constexpr (BF) {
-        if (stream_outputs((long long)B * ss * 2)) sym_gemm<T>(aop, g2, ep, st);
-        else sym_gemm<T>(aop, g2, cached_stores(ep), st);
+        if (stream_outputs((long long)B * ss * 2)) sym_gemm(aop, g2, ep, st);
+        else sym_gemm(aop, g2, cached_stores(ep), st);
       } else {
-        sym_gemm<T>(aop, g2, ep, st);
+        gemm_f32<false, true>(aop, aop, g2, ep, sc.ok, at(sc.a, t), at(sc.a, t), st);
       }
     }
     GemmShape g3{p.s_pad, p.l_pad, p.s_pad, p.s_pad, p.l_pad, ss, sl, B, 1};
@@ -398,7 +403,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
         ef.transpose_out = 0;
         ef.rows_valid = p.s_pad;
         ef.cols_valid = p.l_pad;
-        update_gemm<T>(p, bm, xop(), g3, ef, st);
+        update_gemm(bm, xop(), g3, ef, st);
         continue;
       }
       EpiUpdateHL<T> eu{};
@@ -420,7 +425,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
         eu.rows_valid = p.s;
         eu.cols_valid = p.l;
       }
-      update_gemm<T>(p, bm, xop(), g3, eu, st);
+      update_gemm(bm, xop(), g3, eu, st);
     } else if (!last || p.explicit_restore) {
       EpiUpdate<float, float> eu{};
       eu.x = cur;
@@ -431,7 +436,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       eu.ostride = sl;
       eu.ldo = p.l_pad;
       eu.final_out = 0;
-      update_gemm<T>(p, bm, xop(), g3, eu, st);
+      gemm_f32<true, false>(bm, cur, g3, eu, sc.ok, at(sc.b, t), at(sc.x, t), st);
     } else {
       EpiUpdate<float, T> eu{};
       eu.x = cur;
@@ -445,7 +450,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       eu.transpose_out = p.tall ? 1 : 0;
       eu.rows_valid = p.s;
       eu.cols_valid = p.l;
-      update_gemm<T>(p, bm, xop(), g3, eu, st);
+      gemm_f32<true, false>(bm, cur, g3, eu, sc.ok, at(sc.b, t), at(sc.x, t), st);
     }
     float* tmp = cur;
     cur = nxt;

@@ -1007,15 +1007,23 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
       hn = th;
     }
   }
-  auto sym_gemm = [&](const float* A, const float* B, GemmShape g, const auto& epi) {
+  // fp32 products: operands split into fp16 pairs on the way into LDS when the
+  // table bounds the iterates (split_scales), else fp32 MFMA
+  const auto coef = [&](int t, float& a, float& b, float& c) {
+    a = o.poly ? o.poly[nc * t] : 1.5f;
+    b = o.poly ? o.poly[nc * t + 1] : -0.5f;
+    c = (o.poly && nc == 3) ? o.poly[nc * t + 2] : 0.f;
+  };
+  const SplitScales sc = p.f16 ? SplitScales{} : split_scales(p.steps, std::max(1.f, 1.f / o.gamma), coef);
+  auto sym_gemm = [&](const float* A, const float* B, GemmShape g, const auto& epi, int ea, int eb) {
     g.part = p.split;   // a mostly idle last round is cut along K
     g.part_cap = p.split_cap;
-    launch_gemm<CfgTile128, float, false, true>(A, B, g, epi, st);
+    gemm_f32<false, true>(A, B, g, epi, sc.ok, ea, eb, st);
   };
+  const auto at = [&](const std::vector<int>& v, int t) { return sc.ok ? v[t] : 0; };
   for (int t = 0; t < (p.f16 ? 0 : p.steps); ++t) {
-    const float a = o.poly ? o.poly[nc * t] : 1.5f;
-    const float b = o.poly ? o.poly[nc * t + 1] : -0.5f;
-    const float c = (o.poly && nc == 3) ? o.poly[nc * t + 2] : 0.f;
+    float a, b, c;
+    coef(t, a, b, c);
     GemmShape g{np, np, np, np, np, nn, nn, 1};
     EpiGram eg{};
     eg.stride = nn;
@@ -1029,12 +1037,12 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
     }
     {
       ProfScope ps(SD_STAGE_NS_GRAM, st);
-      sym_gemm(cur, cur, g, eg);
+      sym_gemm(cur, cur, g, eg, at(sc.x, t), at(sc.x, t));
     }
     if (c != 0.f) {
       ProfScope ps(SD_STAGE_NS_POLY, st);
       EpiPoly<float> ep{p.s32, p.bm, b, c, nn, np};
-      sym_gemm(p.s32, p.s32, g, ep);
+      sym_gemm(p.s32, p.s32, g, ep, at(sc.a, t), at(sc.a, t));
     }
     EpiUpdate<float, float> eu{};
     eu.x = cur;
@@ -1046,7 +1054,7 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
     eu.ldo = np;
     {
       ProfScope ps(SD_STAGE_NS_UPDATE, st);
-      sym_gemm(p.bm, cur, g, eu);
+      sym_gemm(p.bm, cur, g, eu, at(sc.b, t), at(sc.x, t));
     }
     float* tmp = cur;
     cur = nxt;
@@ -1068,7 +1076,8 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
     EpiStore es{p.c, nn, np};
     g.part = p.split;
     g.part_cap = p.split_cap;
-    launch_gemm<CfgTile128, float, false, false>(p.r, cur, g, es, st);
+    if (sc.ok) g.dev_exp = p.theta;   // ||R|| <= theta: R scaled by theta's exponent
+    gemm_f32<false, false>(p.r, cur, g, es, sc.ok, 13, at(sc.x, p.steps), st);
   }
   const int tiles = (np / 64) * (np / 64);
   if (K > 0 && p.wk) {
