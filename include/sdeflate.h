@@ -175,7 +175,8 @@ typedef struct {
  * wait for `stream` and are joined back into it, so the results are ready
  * when `stream` reaches that point, as with one call. Each group's result is
  * the one sd_msign_deflated_ex gives for it alone, bit for bit. Scratch comes
- * from the pool on the group's stream unless its opts bring a workspace.
+ * from the pool on `stream` (one block for all groups without a workspace in
+ * their opts; SD_ERR_HIP with nothing enqueued when that allocation fails).
  * The output buffers of different groups must not overlap. */
 int sd_msign_groups(int ngroups, const sd_msign_group* groups, hipStream_t stream);
 
@@ -203,9 +204,8 @@ typedef struct sd_msign_param {
  * first (SD_ERR_INVALID_ARG: count < 1, a null pointer, m or n < 1,
  * k >= min(m, n), or invalid opts; nothing is enqueued then). Staging
  * buffers (two per group, batch x s x l elements) and each group's scratch
- * come from the pool on the group's stream; opts->workspace must be NULL.
- * A pool allocation that fails (SD_ERR_HIP) stops the enqueueing there: the
- * groups enqueued before it still run and are joined into `stream`. */
+ * are one block from the pool on `stream`; opts->workspace must be NULL. When
+ * that allocation fails, SD_ERR_HIP is returned with nothing enqueued. */
 int sd_msign_params(int count, const sd_msign_param* params, int k, int steps, const float* coeffs, int dtype,
                     const sd_msign_opts* opts, hipStream_t stream);
 
