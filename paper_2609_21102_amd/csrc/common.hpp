@@ -110,6 +110,39 @@ __device__ __forceinline__ void state_value8(const uint32_t (&h)[4], uint32_t l0
   }
 }
 
+// The same with an fp16 hi: 2^10 x = hi + res, hi = fp16(2^10 x) and res in an
+// e4m3 byte (scale 2^-8): 15 or more significant bits where 2^-13 <= |x| < 4.
+// v: the scaled values; nh: their fp16 words.
+constexpr float HSTATE = 0x1p10f;          // scale of the fp16 iterate
+constexpr float HSTATE_RES = 0x1p-8f;      // unit of its residual bytes
+constexpr float HSTATE_LIM = 448.f * HSTATE_RES;
+__device__ __forceinline__ float half_lo(uint32_t w) { return (float)__builtin_bit_cast(f16x2_t, w)[0]; }
+__device__ __forceinline__ float half_hi(uint32_t w) { return (float)__builtin_bit_cast(f16x2_t, w)[1]; }
+__device__ __forceinline__ u32x2_t hstate_pack8(const float (&v)[8], const uint32_t (&nh)[4]) {
+  float d[8];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    d[2 * q] = __builtin_amdgcn_fmed3f(v[2 * q] - half_lo(nh[q]), -HSTATE_LIM, HSTATE_LIM);
+    d[2 * q + 1] = __builtin_amdgcn_fmed3f(v[2 * q + 1] - half_hi(nh[q]), -HSTATE_LIM, HSTATE_LIM);
+  }
+  short2_t a = {0, 0}, b = {0, 0};
+  a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(a, d[0], d[1], HSTATE_RES, false);
+  a = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(a, d[2], d[3], HSTATE_RES, true);
+  b = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(b, d[4], d[5], HSTATE_RES, false);
+  b = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(b, d[6], d[7], HSTATE_RES, true);
+  return u32x2_t{__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)};
+}
+__device__ __forceinline__ void hstate_value8(const uint32_t (&h)[4], uint32_t l0, uint32_t l1, float (&x)[8]) {
+  x[0] = half_lo(h[0]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l0, HSTATE_RES, 0);
+  x[1] = half_hi(h[0]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l0, HSTATE_RES, 1);
+  x[2] = half_lo(h[1]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l0, HSTATE_RES, 2);
+  x[3] = half_hi(h[1]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l0, HSTATE_RES, 3);
+  x[4] = half_lo(h[2]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l1, HSTATE_RES, 0);
+  x[5] = half_hi(h[2]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l1, HSTATE_RES, 1);
+  x[6] = half_lo(h[3]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l1, HSTATE_RES, 2);
+  x[7] = half_hi(h[3]) + __builtin_amdgcn_cvt_scalef32_f32_fp8((int)l1, HSTATE_RES, 3);
+}
+
 // Component i (a compile-time constant after unrolling) of a 16-byte value.
 __device__ __forceinline__ uint32_t u4c(const u32x4_t& u, int i) { return u[i]; }
 __device__ __forceinline__ float u4f(const u32x4_t& u, int i) { return __uint_as_float(u[i]); }

@@ -233,6 +233,50 @@ struct EpiPoly {
   }
 };
 
+// Linear combination of the product with one or two fp16 matrices P1, P2 of the
+// same layout (null: absent): v = kc C + k1 P1 + k2 P2, stored as fp16(s16 v)
+// on both triangles and, with out32, in fp32 (upper-triangle and diagonal
+// tiles only, like EpiGramT's). P1 and P2 are loaded before the main loop.
+template <bool STREAM = true>
+struct EpiLin16 {
+  static constexpr bool PRE = true;
+  static constexpr bool ROWWISE = true;
+  static constexpr bool HI_FROM_B = false;
+  const f16_t *p1, *p2;
+  float kc, k1, k2, s16;
+  float* out32;
+  f16_t* out16;
+  long long stride;
+  int ld;
+  __device__ void pre8(int b, int r, int c0, u32x4_t& h, u32x4_t& l) const {
+    const long long o = b * stride + (long long)r * ld + c0;
+    h = ld16(p1 + o);
+    l = p2 ? ld16(p2 + o) : u32x4_t{0u, 0u, 0u, 0u};
+  }
+  __device__ void apply8(int b, int r, int c0, const float (&v)[8], const u32x4_t& h, const u32x4_t& l,
+                         float (&w)[8]) const {
+    float x[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x[2 * q] = fmaf(kc, v[2 * q], fmaf(k1, half_lo(h[q]), k2 * half_lo(l[q])));
+      x[2 * q + 1] = fmaf(kc, v[2 * q + 1], fmaf(k1, half_hi(h[q]), k2 * half_hi(l[q])));
+    }
+    if (out32) {
+      const long long o = b * stride + (long long)r * ld + c0;
+      st16_pol<STREAM>(out32 + o, __builtin_bit_cast(u32x4_t, f32x4_t{x[0], x[1], x[2], x[3]}));
+      st16_pol<STREAM>(out32 + o + 4, __builtin_bit_cast(u32x4_t, f32x4_t{x[4], x[5], x[6], x[7]}));
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = s16 * x[q];
+    store8(b, r, c0, w);
+  }
+  __device__ void store8(int b, int r, int c0, const float (&w)[8]) const {
+    st16_pol<STREAM>(out16 + b * stride + (long long)r * ld + c0,
+                     u32x4_t{pack_h2(w[0], w[1]), pack_h2(w[2], w[3]), pack_h2(w[4], w[5]), pack_h2(w[6], w[7])});
+  }
+  __device__ void operator()(int, int, int, float*, int) const {}
+};
+
 // Iterate update: out = ac * X + C into the next padded iterate, or (final
 // step) into the caller's output: rows < rows_valid, cols < cols_valid, in
 // row-major [rows x cols] or transposed [cols x rows] with its own dtype.
@@ -401,9 +445,8 @@ struct EpiUpdateSymNR {
   }
 };
 
-// Iterate update with the bf16 iterate stored as hi = bf16(X) plus an e4m3
-// residual byte (state_pack8 / state_value8): out = ac * X + C, written in the
-// same form, or (final step) into the caller's output with the rules of
+// Iterate update with the 16-bit iterate stored as hi plus an e4m3 residual
+// byte: out = ac * X + kc C, written in the same form, or (final step) into the caller's output with the rules of
 // EpiUpdate. hi is the product operand of the next step.
 // Row-wise epilogue: the kernel hands it eight consecutive columns of one row
 // (the accumulators pass through LDS), so global accesses are 16 bytes (hi)
@@ -411,17 +454,21 @@ struct EpiUpdateSymNR {
 // product's B operand itself (X, K x N with K = the rows of the iterate), so
 // the kernel copies it out of the LDS ring while the K steps that cover the
 // tile's rows pass through (HI_FROM_B) instead of reading it again from HBM.
-template <typename TO>
+// T16 = f16_t: hi holds 2^10 X in fp16 (hstate_pack8 / hstate_value8), kc
+// takes the product to that scale and the caller's output is scaled back;
+// T16 = bf16_t: hi = bf16(X) (state_pack8 / state_value8), kc = 1.
+template <typename TO, typename T16 = bf16_t>
 struct EpiUpdateHL {
+  static constexpr bool HALF = std::is_same<T16, f16_t>::value;
   static constexpr bool PRE = true;
   static constexpr bool ROWWISE = true;
   static constexpr bool HI_FROM_B = true;
-  const bf16_t* hi;
+  const T16* hi;
   const int8_t* lo;    // residual bytes, same element layout as hi
   long long xstride;
   int ldx;
-  float ac;
-  bf16_t* out_hi;      // next state (same layout as hi / lo)
+  float ac, kc;
+  T16* out_hi;         // next state (same layout as hi / lo)
   int8_t* out_lo;
   TO* out;             // final step: caller output
   long long ostride;
@@ -440,19 +487,25 @@ struct EpiUpdateHL {
                          float (&)[8]) const {
     const uint32_t hw[4] = {h[0], h[1], h[2], h[3]};
     float v[8];
-    state_value8(hw, l[0], l[1], v);
+    if constexpr (HALF) hstate_value8(hw, l[0], l[1], v);
+    else state_value8(hw, l[0], l[1], v);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = ac * v[q] + acc[q];
+    for (int q = 0; q < 8; ++q) v[q] = HALF ? fmaf(kc, acc[q], ac * v[q]) : ac * v[q] + acc[q];
     if (!final_out) {
       uint32_t nh[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) nh[q] = pack_bf2(v[2 * q], v[2 * q + 1]);
+      for (int q = 0; q < 4; ++q) nh[q] = Op16<T16>::pack2(v[2 * q], v[2 * q + 1]);
       const long long o = b * xstride + (long long)r * ldx + c0;
       st16_nt(out_hi + o, u32x4_t{nh[0], nh[1], nh[2], nh[3]});
-      st8_nt(out_lo + o, state_pack8(v, nh));
+      if constexpr (HALF) st8_nt(out_lo + o, hstate_pack8(v, nh));
+      else st8_nt(out_lo + o, state_pack8(v, nh));
       return;
     }
     if (r >= rows_valid) return;
+    if constexpr (HALF) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] *= 1.f / HSTATE;
+    }
     TO* ob = out + b * ostride;
     if (!transpose_out) {
       if constexpr (sizeof(TO) == 2) {
@@ -644,6 +697,8 @@ using CfgTile64 = GemmCfg<2, 2, 1, 1>;           // 64 x 64, 256 threads
 // Direct-to-LDS kernel: 128 x 128, two-stage ring, two work-groups per CU.
 using CfgDma128 = GemmCfg<2, 2, 2, 2, 2, 2>;
 using CfgDma256 = GemmCfg<2, 4, 4, 2, 2, 2>;   // 256 x 256, eight waves, one work-group per CU
+using CfgDma64 = GemmCfg<2, 2, 1, 1, 4, 2>;    // 64 x 64, four-stage ring, two work-groups per CU
+using CfgDma64x4 = GemmCfg<2, 2, 1, 1, 2, 4>;  // 64 x 64, two-stage ring, four work-groups per CU
 
 // Eight floats (two 16-byte words) rounded to eight 16-bit operands of type T.
 template <typename T>
@@ -1653,6 +1708,9 @@ EpiGramT<T16, RW, false> cached_stores(const EpiGramT<T16, RW, true>& e) {
 template <typename TO>
 EpiPoly<TO, false> cached_stores(const EpiPoly<TO, true>& e) {
   return EpiPoly<TO, false>{e.a32, e.out, e.bc, e.cc, e.stride, e.ld};
+}
+inline EpiLin16<false> cached_stores(const EpiLin16<true>& e) {
+  return EpiLin16<false>{e.p1, e.p2, e.kc, e.k1, e.k2, e.s16, e.out32, e.out16, e.stride, e.ld};
 }
 
 // Host launcher (errors surface through hipGetLastError at the end of a call).

@@ -41,8 +41,10 @@ struct LowRankArgs {
   void* out;          // null: no output
   long long so;
   int ldo;
-  bf16_t* out16;      // optional bf16 copy of out (same layout)
-  int8_t* out_lo;     // with out16: e4m3 residual byte of out against bf16(out) (state_pack8)
+  bf16_t* out16;      // optional iterate state: bf16(out) (same layout), with
+  int8_t* out_lo;     // the e4m3 residual bytes against it (state_pack8)
+  f16_t* outh;        // optional iterate state: fp16(2^10 out), with its residual
+                      // bytes in out_lo (hstate_pack8)
   f16_t* xs16;        // optional fp16(alpha * x) (same layout as out)
   float* sumsq;       // [b][tiles] or null
   int rows_pad, cols_pad, kmax, batch;
@@ -240,7 +242,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
       for (int q = 0; q < 4; ++q) nh[q] = pack_bf2(v[2 * q], v[2 * q + 1]);
       const long long o = b * a.so + (long long)i * a.ldo + n0 + cg * 8;
       st16_nt(a.out16 + o, u32x4_t{nh[0], nh[1], nh[2], nh[3]});
-      if (a.out_lo) st8_nt(a.out_lo + o, state_pack8(v, nh));
+      st8_nt(a.out_lo + o, state_pack8(v, nh));
+    } else if (a.outh) {
+      uint32_t nh[4];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) v[c] *= HSTATE;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) nh[q] = pack_h2(v[2 * q], v[2 * q + 1]);
+      const long long o = b * a.so + (long long)i * a.ldo + n0 + cg * 8;
+      st16_nt(a.outh + o, u32x4_t{nh[0], nh[1], nh[2], nh[3]});
+      st8_nt(a.out_lo + o, hstate_pack8(v, nh));
     }
   }
   if (a.sumsq) {

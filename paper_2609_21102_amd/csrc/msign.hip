@@ -127,16 +127,40 @@ static void make_plan(MsignPlan& p, int batch, int m, int n, int k, int steps, i
 // Iterate update X <- a X + B X on 128 x 128 tiles; the epilogue's X reads
 // are issued before the main loop. Operand tiles move into a two-stage LDS
 // ring by direct-to-LDS loads, two work-groups per CU.
-template <typename Epi>
-static void update_gemm(const bf16_t* bm, const bf16_t* xop, const GemmShape& g, const Epi& eu, hipStream_t st) {
+template <typename T, typename Epi>
+static void update_gemm(const T* bm, const T* xop, const GemmShape& g, const Epi& eu, hipStream_t st) {
   launch_gemm_dma<CfgDma128, true, false>(bm, xop, g, eu, st);
 }
 
-// Symmetric products (Gram and A^2) on 128 x 128 tiles, upper-triangle tiles
-// only; direct-to-LDS loads.
-template <typename Epi>
-static void sym_gemm(const bf16_t* a, const GemmShape& g, const Epi& e, hipStream_t st) {
-  launch_gemm_dma<CfgDma128, false, true>(a, a, g, e, st);
+// Symmetric products (Gram and the s x s side) on upper-triangle tiles only;
+// direct-to-LDS loads.
+// The outputs are read by the next launch: ordinary stores when they
+// fit in half of the last-level cache (stream_outputs).
+template <typename T, typename Epi>
+static void sym_gemm(const T* a, const T* b, const GemmShape& g, const Epi& e, long long out_bytes, hipStream_t st) {
+  if (stream_outputs(out_bytes)) {
+    launch_gemm_dma<CfgDma128, false, true>(a, b, g, e, st);
+    return;
+  }
+  const auto c = cached_stores(e);
+  if constexpr (std::is_same<T, f16_t>::value) {
+    // Few tiles leave CUs idle and each K loop bound by its loads' latency
+    // (0.9 us per K step of 64 at one work-group per CU): 64 x 64 tiles, with a
+    // four-stage ring while two work-groups per CU hold the grid, else two
+    // stages and four work-groups. 1 x 768 x 3072: 517 -> 345 us per call;
+    // 12 x 768 x 768 (252 tiles): 843 -> 814 us; at 504 tiles equal and at 990
+    // the operand traffic costs 4%.
+    const long long tm = g.M / 128, blocks = tm * (tm + 1) / 2 * g.batch;
+    if (blocks <= 128) {
+      launch_gemm_dma<CfgDma64, false, true>(a, b, g, c, st);
+      return;
+    }
+    if (blocks <= 384) {
+      launch_gemm_dma<CfgDma64x4, false, true>(a, b, g, c, st);
+      return;
+    }
+  }
+  launch_gemm_dma<CfgDma128, false, true>(a, b, g, c, st);
 }
 
 // Residual floor rho of the padded start, relative to ||X||_F: the rounding
@@ -148,6 +172,129 @@ static void sym_gemm(const bf16_t* a, const GemmShape& g, const Epi& e, hipStrea
 // ||X||_F; a residual within rho = 16 u = 2^-20 of ||X||_F is that rounding
 // (the input has rank <= k_eff, outside Alg. 1's k < rank(M)) and is dropped.
 constexpr float kResidualFloor = 0x1p-20f;
+
+// The bf16 path's filter on fp16 operands (tables that split_scales admits):
+// groups of steps on the s x s side (filter_groups), iterate state as fp16 hi
+// plus a residual byte. The step-by-step form was bound by its passes over X
+// and the latency of its K loops (24 x 768 x 3072, five steps: 69 us per Gram,
+// 29 per polynomial, 130 per update; 28% MFMA busy); fp16 takes bf16's place at
+// the same MFMA rate with three more bits per operand, and that is what lets
+// steps share one Gram and one update: 1414 -> 1153 us per call (two Grams, two
+// updates, fourteen s x s products of about 30 us), undeflated 1212 -> 924 us
+// (one step per group: 1271), 1 x 1280 x 5120 623 -> 270. Groups of more than
+// one step need l_pad >= 2 s_pad: their extra s x s matrices lie in the next
+// iterate's buffers, idle until the update, and below r = 2 the flops saved
+// are few (12 x 768 x 768 takes the same time either way).
+template <typename Coef>
+static void filter_half(const MsignPlan& p, Coef coef, const SplitScales& sc, bf16_t* out, hipStream_t st) {
+  const int B = p.batch;
+  const long long sl = (long long)p.s_pad * p.l_pad, ss = (long long)p.s_pad * p.s_pad, B16 = (long long)B * ss * 2;
+  f16_t* cur = reinterpret_cast<f16_t*>(p.xa16);
+  f16_t* nxt = reinterpret_cast<f16_t*>(p.xb16);
+  int8_t *curlo = p.xalo, *nxtlo = p.xblo;
+  f16_t* const a16 = reinterpret_cast<f16_t*>(p.a16);
+  f16_t* const bm = reinterpret_cast<f16_t*>(p.bm);
+  const GemmShape gs{p.s_pad, p.s_pad, p.s_pad, p.s_pad, p.s_pad, ss, ss, B};
+  const auto pw = [](int e) { return std::ldexp(1.f, e); };
+  const std::vector<FilterGroup> groups = filter_groups(p.steps, p.l_pad >= 2 * p.s_pad ? 3 : 1, p.s, sc, coef);
+  for (size_t gi = 0; gi < groups.size(); ++gi) {
+    const FilterGroup& f = groups[gi];
+    const bool last = gi + 1 == groups.size();
+    f16_t* const w16 = nxt;                    // P_i A_i
+    f16_t* const b1 = nxt + (long long)B * ss; // odd steps' B_i
+    f16_t* const q1 = reinterpret_cast<f16_t*>(nxtlo);   // Q_1 of a group of three
+    float a, b, c, qa;
+    coef(f.t0, a, b, c);
+    qa = a;
+    int ea = sc.a[f.t0];
+    {
+      ProfScope ps(SD_STAGE_NS_GRAM, st);
+      const GemmShape g{p.s_pad, p.s_pad, p.l_pad, p.l_pad, p.l_pad, sl, sl, B};
+      EpiGramT<f16_t> e{};
+      e.stride = ss;
+      e.ld = p.s_pad;
+      const float unit = 1.f / (HSTATE * HSTATE);
+      if (f.g == 1 && c == 0.f) {   // B = b A directly
+        e.out16 = bm;
+        e.scale16 = b * unit * pw(f.eq[0]);
+      } else {
+        e.out32 = p.a32;
+        e.scale32 = unit;
+        e.out16 = a16;
+        e.scale16 = unit * pw(ea);
+      }
+      sym_gemm(cur, cur, g, e, (long long)B * ss * (e.out32 ? 6 : 2), st);
+    }
+    const f16_t* q = bm;   // Q_i - qa I, exponent eq
+    int eq = f.eq[0];
+    for (int i = 0; i < f.g; ++i) {
+      ProfScope ps(SD_STAGE_NS_POLY, st);
+      const int t = f.t0 + i, eb = sc.b[t];
+      coef(t, a, b, c);
+      f16_t* const bi = i == 1 ? b1 : bm;
+      if (f.g > 1 || c != 0.f) {   // B_i = b A_i + c A_i^2
+        const EpiPoly<f16_t> e{p.a32, bi, b * pw(eb), c * pw(eb - 2 * ea), ss, p.s_pad};
+        sym_gemm<f16_t>(a16, a16, gs, e, B16, st);
+      }
+      if (i + 1 < f.g) {           // W = P_i A_i
+        const EpiPoly<f16_t> e{p.a32, w16, a * pw(ea), pw(-eb), ss, p.s_pad};
+        sym_gemm<f16_t>(bi, a16, gs, e, B16, st);
+      }
+      if (i > 0) {                 // Q_i = P_i Q_{i-1}
+        f16_t* const qn = i + 1 < f.g ? q1 : a16;
+        const EpiLin16<> e{q, bi, pw(-eq - eb), a * pw(-eq), qa * pw(-eb), pw(f.eq[i]), nullptr, qn, ss, p.s_pad};
+        sym_gemm<f16_t>(bi, q, gs, e, B16, st);
+        q = qn;
+        eq = f.eq[i];
+        qa *= a;
+      }
+      if (i + 1 < f.g) {           // A_{i+1} = W P_i
+        const int en = sc.a[t + 1];
+        const EpiLin16<> e{w16, nullptr, pw(-ea - eb), a * pw(-ea), 0.f, pw(en), p.a32, a16, ss, p.s_pad};
+        sym_gemm<f16_t>(w16, bi, gs, e, 3 * B16, st);
+        ea = en;
+      }
+    }
+    ProfScope ps(SD_STAGE_NS_UPDATE, st);
+    const GemmShape g{p.s_pad, p.l_pad, p.s_pad, p.s_pad, p.l_pad, ss, sl, B, 1};
+    const auto update = [&](auto eu) {
+      eu.hi = cur;
+      eu.lo = curlo;
+      eu.xstride = sl;
+      eu.ldx = p.l_pad;
+      eu.ac = qa;
+      eu.kc = pw(-eq);
+      if (!last) {
+        eu.out_hi = nxt;
+        eu.out_lo = nxtlo;
+      }
+      update_gemm<f16_t>(q, cur, g, eu, st);
+    };
+    if (last && p.explicit_restore) {
+      // the filter output stays float32 (canonical layout) for the restore
+      EpiUpdateHL<float, f16_t> eu{};
+      eu.out = p.xl32;
+      eu.ostride = sl;
+      eu.ldo = p.l_pad;
+      eu.final_out = 1;
+      eu.rows_valid = p.s_pad;
+      eu.cols_valid = p.l_pad;
+      update(eu);
+    } else {
+      EpiUpdateHL<bf16_t, f16_t> eu{};
+      eu.out = out;
+      eu.ostride = (long long)p.m * p.n;
+      eu.ldo = p.tall ? p.s : p.l;
+      eu.final_out = last ? 1 : 0;
+      eu.transpose_out = p.tall ? 1 : 0;
+      eu.rows_valid = p.s;
+      eu.cols_valid = p.l;
+      update(eu);
+    }
+    std::swap(cur, nxt);
+    std::swap(curlo, nxtlo);
+  }
+}
 
 template <typename T>
 static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opts& o, const T* in, T* out,
@@ -271,6 +418,22 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
     hipLaunchKernelGGL(fill_int_kernel, grid1(B, 256), dim3(256), 0, st, o.k_eff_out, (long long)B, 0);
   }
 
+  const auto coef = [&](int t, float& a, float& b, float& c) {
+    a = coeffs ? coeffs[3 * t] : 3.4445f;
+    b = coeffs ? coeffs[3 * t + 1] : -4.7750f;
+    c = coeffs ? coeffs[3 * t + 2] : 2.0315f;
+  };
+  // scales of the filter's fp16 products (fp32 path: split pairs), where the
+  // table bounds the iterates; ||X0|| is at most 1 (residual) next to
+  // 1 / gamma (padded head)
+  const SplitScales sc = split_scales(
+      p.steps, p.k > 0 && !p.explicit_restore ? std::max(1.f, 1.f / o.gamma) : 1.f, coef);
+  // bf16 path: fp16 operands (filter_half). Below s = 32 the steps stay bf16
+  // products: so few rounding errors do not average out, and the two forms
+  // differ by up to 3e-2 there (1 x 37), for 10 us of launches (8 x 16 x 300:
+  // 121 against 132 us).
+  const bool half = sizeof(T) == 2 && sc.ok && p.steps > 0 && p.s >= 32;
+
   // Alg. 1: residual norm and padded start
   LowRankArgs la{};
   la.x = xc;
@@ -308,7 +471,8 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
   la.coef2 = R64 ? p.coefG : nullptr;
   la.alpha = p.alpha;
   la.out = p.xa;        // fp32 path: float32 X0
-  la.out16 = p.xa16;    // bf16 path: X0 as hi plus 8-bit residuals
+  if (half) la.outh = reinterpret_cast<f16_t*>(p.xa16);   // bf16 path: X0 as hi plus 8-bit residuals
+  else la.out16 = p.xa16;
   la.out_lo = p.xalo;
   la.so = sl;
   la.ldo = p.l_pad;
@@ -329,18 +493,11 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
     if constexpr (BF) return reinterpret_cast<const T*>(cur16);
     else return reinterpret_cast<const T*>(cur);
   };
-  const auto coef = [&](int t, float& a, float& b, float& c) {
-    a = coeffs ? coeffs[3 * t] : 3.4445f;
-    b = coeffs ? coeffs[3 * t + 1] : -4.7750f;
-    c = coeffs ? coeffs[3 * t + 2] : 2.0315f;
-  };
-  // fp32 path: products on split fp16 pairs where the table bounds the
-  // iterates; ||X0|| is at most 1 (residual) next to 1 / gamma (padded head)
-  const SplitScales sc = BF ? SplitScales{}
-                            : split_scales(p.steps, p.k > 0 && !p.explicit_restore ? std::max(1.f, 1.f / o.gamma) : 1.f,
-                                           coef);
   const auto at = [&](const std::vector<int>& v, int t) { return sc.ok ? v[t] : 0; };
-  for (int t = 0; t < p.steps; ++t) {
+  if constexpr (BF) {
+    if (half) filter_half(p, coef, sc, out, st);
+  }
+  for (int t = 0; t < (half ? 0 : p.steps); ++t) {
     float a, b, c;
     coef(t, a, b, c);
     GemmShape g1{p.s_pad, p.s_pad, p.l_pad, p.l_pad, p.l_pad, sl, sl, B};
@@ -359,15 +516,10 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       eg.out32 = reinterpret_cast<float*>(bm);
       eg.scale32 = b;
     }
-    // bf16 path: the Gram's copies and B stay cacheable for their reader
-    // when small enough (stream_outputs)
     {
       ProfScope ps(SD_STAGE_NS_GRAM, st);
       if constexpr (BF) {
-        if (stream_outputs((long long)B * ss * ((eg.out32 ? 4 : 0) + (eg.out16 ? 2 : 0))))
-          sym_gemm(xop(), g1, eg, st);
-        else
-          sym_gemm(xop(), g1, cached_stores(eg), st);
+        sym_gemm(xop(), xop(), g1, eg, (long long)B * ss * ((eg.out32 ? 4 : 0) + (eg.out16 ? 2 : 0)), st);
       } else {
         gemm_f32<false, true>(cur, cur, g1, eg, sc.ok, at(sc.x, t), at(sc.x, t), st);
       }
@@ -378,8 +530,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       const T* aop = BF ? reinterpret_cast<const T*>(p.a16) : reinterpret_cast<const T*>(p.a32);
       ProfScope ps(SD_STAGE_NS_POLY, st);
       if constexpr (BF) {
-        if (stream_outputs((long long)B * ss * 2)) sym_gemm(aop, g2, ep, st);
-        else sym_gemm(aop, g2, cached_stores(ep), st);
+        sym_gemm(aop, aop, g2, ep, (long long)B * ss * 2, st);
       } else {
         gemm_f32<false, true>(aop, aop, g2, ep, sc.ok, at(sc.a, t), at(sc.a, t), st);
       }
@@ -475,6 +626,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
     ra.coef2 = nullptr;
     ra.alpha = nullptr;
     ra.out16 = nullptr;
+    ra.outh = nullptr;
     ra.out_lo = nullptr;
     ra.sumsq = nullptr;
     const bool direct = !p.copy_in && reinterpret_cast<uintptr_t>(out) % 16 == 0;
