@@ -388,15 +388,14 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
       ProfScope ps(SD_STAGE_SMALL, st);
       gram_partials(pg, sg_, lg, pg, sg_, lg, rp, rp, lg, true, p.part, B, st);   // G G^T
 #define SD_HEAD(NPV)                                                                                       \
-  hipLaunchKernelGGL(svd_head_kernel<NPV>, dim3(B), dim3(SM_THREADS), 0, st, p.part, lg / GP_CHUNK, rp, p.kw, \
+  hipLaunchKernelGGL(svd_head_kernel<NPV>, dim3(B), dim3(JacobiThreads<NPV>::value), 0, st, p.part, lg / GP_CHUNK, rp, p.kw, \
                      p.k, o.tau, p.E, p.sv, p.invsv, p.keff, p.coefA, o.s_out, o.k_eff_out)
       switch (jacobi_class(rp)) {
         case 4: SD_HEAD(4); break;
         case 8: SD_HEAD(8); break;
         case 12: SD_HEAD(12); break;
         case 16: SD_HEAD(16); break;
-        case 32: SD_HEAD(32); break;
-        default: SD_HEAD(0); break;
+        default: SD_HEAD(32); break;
       }
 #undef SD_HEAD
       // V = G^T E / s onto the G side's factor, U = Q E onto the Q side's
