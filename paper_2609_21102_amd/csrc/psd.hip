@@ -1064,6 +1064,7 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
   // C = theta fp16(R / theta) fp16(g), the operands the filter left behind
   ProfScope ps(SD_STAGE_RESTORE, st);
   GemmShape g{np, np, np, np, np, nn, nn, 1};
+  g.band = SYM_BAND;
   if (p.f16 && p.wide) {
     EpiScaleStore<false> es{p.c, p.theta, nn, np};
     g.part = p.split;
