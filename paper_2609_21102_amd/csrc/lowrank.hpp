@@ -20,6 +20,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "gemm.hpp"
 
 namespace sd {
 
@@ -353,9 +354,13 @@ static __global__ void rows_to_panel_kernel(const float* in, int c, int len, int
 //   P = (P_raw + P_raw^T) / 2 = (R + R^T) / 4 + (C + C^T) / 4 + H.
 // Every term is evaluated so that P[i][j] and P[j][i] see the same operations
 // on swapped operands (sums are commutative, H uses cp * (u_i u_j)), hence P
-// is exactly symmetric. 64 x 64 tiles; the transposed tiles and the head's
-// coefficients go through LDS (a coefficient read from global memory inside
-// the head sum was re-read after every store, which may alias it).
+// is exactly symmetric. One work-group per pair of 64 x 64 tiles (i, j), (j, i),
+// i <= j: it reads both tiles of R and C once, forms the values of one and
+// writes them to both (a work-group per tile read every tile twice, in 4-byte
+// accesses: n = 16384 2.56 ms against 0.87 now, 3.7 TB/s). Thread (row group, column quad) moves
+// 16 bytes at a time; the transposed tiles and the mirrored values go through
+// LDS. The head's coefficients are in LDS too (a coefficient read from global
+// memory inside the head sum was re-read after every store, which may alias it).
 template <int KM>
 __global__ __launch_bounds__(256) void psd_out_kernel(const float* __restrict__ R, const float* __restrict__ C,
                                                       int ld, const float* __restrict__ Ut, int ldu,
@@ -364,17 +369,32 @@ __global__ __launch_bounds__(256) void psd_out_kernel(const float* __restrict__ 
   __shared__ float ct[64][65];
   __shared__ float rt[64][65];
   __shared__ float ui[KM][64];
-  __shared__ float uj[KM][64];
+  __shared__ __attribute__((aligned(16))) float uj[KM][64];
   __shared__ float cps[KM];
   const int tiles = n_pad / 64;
-  const int i0 = (blockIdx.x / tiles) * 64, j0 = (blockIdx.x % tiles) * 64;
+  int ti = 0, tj = 0;
+  sym_tile(blockIdx.x, tiles, ti, tj);
+  const int i0 = ti * 64, j0 = tj * 64;
   const int tid = threadIdx.x;
   const int kk = kk_dev ? *kk_dev : 0;
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    const long long src = (long long)(j0 + r) * ld + i0 + c;   // element (j0 + r, i0 + c)
-    ct[c][r] = C[src];
-    rt[c][r] = R[src];
+  const int rg = tid >> 4, c4 = 4 * (tid & 15);   // rows rg + 16 u, columns c4 .. c4 + 3
+  float4 ra[4], ca[4], rb[4], cb[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const long long d = (long long)(i0 + rg + 16 * u) * ld + j0 + c4, t = (long long)(j0 + rg + 16 * u) * ld + i0 + c4;
+    ra[u] = *reinterpret_cast<const float4*>(R + d);
+    ca[u] = *reinterpret_cast<const float4*>(C + d);
+    rb[u] = *reinterpret_cast<const float4*>(R + t);
+    cb[u] = *reinterpret_cast<const float4*>(C + t);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const float rv[4] = {rb[u].x, rb[u].y, rb[u].z, rb[u].w}, cv[4] = {cb[u].x, cb[u].y, cb[u].z, cb[u].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      rt[c4 + q][rg + 16 * u] = rv[q];
+      ct[c4 + q][rg + 16 * u] = cv[q];
+    }
   }
   for (int e = tid; e < kk * 64; e += 256) {
     const int p = e >> 6, x = e & 63;
@@ -383,14 +403,46 @@ __global__ __launch_bounds__(256) void psd_out_kernel(const float* __restrict__ 
   }
   if (tid < kk) cps[tid] = coef_p[tid];
   __syncthreads();
-  const int tx = tid & 63, ty = tid >> 6;
-  for (int r = ty; r < 64; r += 4) {
-    const int i = i0 + r, j = j0 + tx;
-    float h = 0.f;
-    for (int p = 0; p < kk; ++p) h = fmaf(cps[p], ui[p][r] * uj[p][tx], h);
-    const long long ij = (long long)i * ld + j;
-    const float v = 0.25f * (R[ij] + rt[r][tx]) + 0.25f * (C[ij] + ct[r][tx]) + h;
-    if (i < n && j < n) out[(long long)i * n + j] = v;
+  const bool vec = n % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+  const auto store = [&](int i, int j, const float (&v)[4]) {   // row i, columns j .. j + 3
+    if (i >= n) return;
+    float* o = out + (long long)i * n + j;
+    if (vec) {
+      if (j < n) *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (j + q < n) o[q] = v[q];
+  };
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = rg + 16 * u;
+    float h[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < kk; ++p) {
+      const float4 w = *reinterpret_cast<const float4*>(&uj[p][c4]);
+      const float a = ui[p][r], c = cps[p];
+      h[0] = fmaf(c, a * w.x, h[0]);
+      h[1] = fmaf(c, a * w.y, h[1]);
+      h[2] = fmaf(c, a * w.z, h[2]);
+      h[3] = fmaf(c, a * w.w, h[3]);
+    }
+    const float rv[4] = {ra[u].x, ra[u].y, ra[u].z, ra[u].w}, cv[4] = {ca[u].x, ca[u].y, ca[u].z, ca[u].w};
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = 0.25f * (rv[q] + rt[r][c4 + q]) + 0.25f * (cv[q] + ct[r][c4 + q]) + h[q];
+      rt[r][c4 + q] = v[q];   // this thread's own entry: the mirrored copy
+    }
+    store(i0 + r, j0 + c4, v);
+  }
+  if (ti == tj) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = rg + 16 * u;
+    const float v[4] = {rt[c4][r], rt[c4 + 1][r], rt[c4 + 2][r], rt[c4 + 3][r]};
+    store(j0 + r, i0 + c4, v);
   }
 }
 

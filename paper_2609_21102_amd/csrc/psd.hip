@@ -1080,7 +1080,7 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
     if (sc.ok) g.dev_exp = p.theta;   // ||R|| <= theta: R scaled by theta's exponent
     gemm_f32<false, false>(p.r, cur, g, es, sc.ok, 13, at(sc.x, p.steps), st);
   }
-  const int tiles = (np / 64) * (np / 64);
+  const int tiles = (np / 64) * (np / 64 + 1) / 2;
   if (K > 0 && p.wk) {
     // the head as 2 U max(lam, 0) U^T added to C: the output's (C + C^T) / 4
     // then carries (H + H^T) / 2, exactly symmetric
@@ -1118,16 +1118,35 @@ __global__ __launch_bounds__(256) void admm_y_kernel(const float* __restrict__ X
   y[i] = b[i] * inv_sigma - (X[d] * inv_sigma + S[d] - C[d]);
 }
 
-// Z = C - Diag(y) - X / sigma (row by row: work-group g takes rows g,
-// g + gridDim.x, ...; no division per element)
+// Z = C - Diag(y) - X / sigma into the padded [np][np] buffer that the
+// projection reads (its zero padding is written once per call); row by row:
+// work-group g takes rows g, g + gridDim.x, .... VEC: four elements per
+// thread (n a multiple of 4, C and X 16-byte aligned).
+template <bool VEC>
 __global__ __launch_bounds__(256) void admm_z_kernel(const float* __restrict__ C, const float* __restrict__ X,
                                                      const float* __restrict__ y, int n, float inv_sigma,
-                                                     float* __restrict__ Z) {
+                                                     float* __restrict__ Z, int np) {
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const long long r = (long long)i * n;
-    for (int j = threadIdx.x; j < n; j += blockDim.x)
-      Z[r + j] = C[r + j] - (i == j ? y[i] : 0.f) - X[r + j] * inv_sigma;
+    const long long r = (long long)i * n, z = (long long)i * np;
+    const float yi = y[i];
+    if constexpr (VEC) {
+      for (int j = 4 * threadIdx.x; j < n; j += 4 * blockDim.x) {
+        const float4 c = *reinterpret_cast<const float4*>(C + r + j), x = *reinterpret_cast<const float4*>(X + r + j);
+        *reinterpret_cast<float4*>(Z + z + j) =
+            make_float4(c.x - (i == j ? yi : 0.f) - x.x * inv_sigma, c.y - (i == j + 1 ? yi : 0.f) - x.y * inv_sigma,
+                        c.z - (i == j + 2 ? yi : 0.f) - x.z * inv_sigma, c.w - (i == j + 3 ? yi : 0.f) - x.w * inv_sigma);
+      }
+    } else {
+      for (int j = threadIdx.x; j < n; j += blockDim.x)
+        Z[z + j] = C[r + j] - (i == j ? yi : 0.f) - X[r + j] * inv_sigma;
+    }
   }
+}
+
+// Zero padding of Z: rows n .. np - 1 and columns n .. np - 1.
+__global__ __launch_bounds__(256) void admm_pad_kernel(float* __restrict__ Z, int n, int np) {
+  for (int i = blockIdx.x; i < np; i += gridDim.x)
+    for (int j = (i < n ? n : 0) + threadIdx.x; j < np; j += blockDim.x) Z[(long long)i * np + j] = 0.f;
 }
 
 // X <- X + sigma (S + Diag(y) - C), and per-block float64 partial sums of
@@ -1178,11 +1197,13 @@ __global__ __launch_bounds__(256) void admm_cnorm_kernel(const float* __restrict
 // workspace (planned for Z, which the arena aligns to 256 bytes).
 static void admm_plan(PsdPlan& p, Arena& ar, int n, int k, int steps, const sd_psd_opts& o, float** Z = nullptr,
                       double** part = nullptr, double** cpart = nullptr) {
-  float* z = ar.take<float>((size_t)n * n);
+  const size_t np = (size_t)round_up(n, 128);
+  float* z = ar.take<float>(np * np);   // padded: read in place by the projection
   double* pa = ar.take<double>(3 * ADMM_BLOCKS);
   double* cp = ar.take<double>(ADMM_BLOCKS);
   // sizing (no base) plans with an aligned stand-in address: same copy-in decision
   make_psd_plan(p, n, k, steps, ar.base ? z : reinterpret_cast<const float*>(uintptr_t(256)), o);
+  p.copy_in = false;
   plan_psd(p, ar);
   if (Z) *Z = z;
   if (part) *part = pa;
@@ -1352,9 +1373,14 @@ int sd_admm_diag(int n, int iters, int steps, float sigma, const float* C, const
   admm_plan(p, ar, n, k, steps, o, &Z, &part, &cpart);
   const float inv_sigma = 1.f / sigma;
   hipLaunchKernelGGL(admm_cnorm_kernel, dim3(ADMM_BLOCKS), dim3(256), 0, stream, C, n, cpart);
+  if (p.n_pad != n) hipLaunchKernelGGL(admm_pad_kernel, dim3(ADMM_BLOCKS), dim3(256), 0, stream, Z, n, p.n_pad);
+  const bool vec = n % 4 == 0 && (reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(X)) % 16 == 0;
   for (int it = 0; it < iters && rc == SD_OK; ++it) {
     hipLaunchKernelGGL(admm_y_kernel, grid1(n, 256), dim3(256), 0, stream, X, S, C, b, n, inv_sigma, y);
-    hipLaunchKernelGGL(admm_z_kernel, dim3(ADMM_BLOCKS), dim3(256), 0, stream, C, X, y, n, inv_sigma, Z);
+    if (vec)
+      hipLaunchKernelGGL(admm_z_kernel<true>, dim3(ADMM_BLOCKS), dim3(256), 0, stream, C, X, y, n, inv_sigma, Z, p.n_pad);
+    else
+      hipLaunchKernelGGL(admm_z_kernel<false>, dim3(ADMM_BLOCKS), dim3(256), 0, stream, C, X, y, n, inv_sigma, Z, p.n_pad);
     sd_psd_opts oi = o;
     if (it < warmup) oi.tau = 1e-30f;   // gate held closed: s_r < tau s_1 cannot hold
     oi.n_deflated_out = ndef_out ? ndef_out + it : nullptr;
