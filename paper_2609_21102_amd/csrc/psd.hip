@@ -78,16 +78,21 @@ __global__ __launch_bounds__(1024) void lanczos_init_kernel(float* Q, int n, int
 
 // One Lanczos step on B = R^2 with w = B q_j already computed, on one
 // work-group (n_pad below 8192: one launch instead of four):
-//   alpha_j = q_j . w;  w -= alpha_j q_j + beta_{j-1} q_{j-1};
-//   two classical Gram-Schmidt passes against q_0..q_j;
+//   pass 1: h_v = q_v . w for v <= j;  w -= sum_v h_v q_v, alpha_j = h_j (this
+//           subtracts the three-term recurrence's alpha_j q_j and beta_{j-1}
+//           q_{j-1} and a first classical Gram-Schmidt pass in one);
+//   pass 2: the same on the result;
 //   beta_j = ||w||; q_{j+1} = w / beta_j (a zero beta ends the run).
-// Thread t keeps the float4 chunks t and t + 1024 of w in registers for the
-// whole step; the basis vectors are read four at a time with every load of
-// a batch issued before its first use (a loop that waited on each load made
-// the step a chain of memory round trips), and a pass's products are
-// reduced per wave, then over the waves, with one barrier.
-constexpr int LS_CH = 2;   // float4 chunks per thread: n_pad / 4 <= 2048
-constexpr int LS_B = 4;    // basis vectors per load batch
+// Thread t of NT keeps the float4 chunks t + NT c of w in registers for the whole
+// step, and the first KEEP basis vectors too, loaded once, all loads in
+// flight together (later ones are read in batches of four, in both passes and
+// both directions). Four products are summed over the wave at a time, halving
+// the values with the lanes (7 exchanges instead of 24), every wave adds the
+// waves' partial sums itself, and a pass takes one barrier: 24 -> 7.0 us per
+// step at n = 1000, 25.7 -> 22.3 at n = 5000. CH and KEEP about fill
+// the 256 registers of a thread of 512 (1024 threads with two chunks each took
+// 23.4 us at n = 5000).
+constexpr int LS_B = 4;    // basis vectors per batch
 // p[i] when ok, else zeros; the load always reads an in-bounds element (p[0]
 // when not ok) and the zeros are a value select, so the pointer stays a
 // global one (selecting between a global element and a local zero made
@@ -103,101 +108,129 @@ __device__ __forceinline__ float ld_or0(const float* __restrict__ p, long long i
 __device__ __forceinline__ double dot4(const float4& a, const float4& b) {
   return (double)a.x * b.x + (double)a.y * b.y + (double)a.z * b.z + (double)a.w * b.w;
 }
-__global__ __launch_bounds__(1024) void lanczos_step_kernel(float* Q, int n_pad, float* w, int j, int m,
+// Sums over the wave of d[0..3]: lane l gets the sum of d[2 (l / 32) + (l / 16) % 2].
+__device__ __forceinline__ double wave_sum4(const double (&d)[LS_B]) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const bool b5 = lane & 32, b4 = lane & 16;
+  const double x0 = (b5 ? d[2] : d[0]) + __shfl_xor(b5 ? d[0] : d[2], 32, WAVE);
+  const double x1 = (b5 ? d[3] : d[1]) + __shfl_xor(b5 ? d[1] : d[3], 32, WAVE);
+  double y = (b4 ? x1 : x0) + __shfl_xor(b4 ? x0 : x1, 16, WAVE);
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) y += __shfl_xor(y, o, WAVE);
+  return y;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {   // lane uniform
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+template <int LS_NT, int CH, int KEEP>
+__global__ __launch_bounds__(LS_NT) void lanczos_step_kernel(float* Q, int n_pad, float* w, int j, int m,
                                                             LanczosState* st) {
-  __shared__ double red[16];
-  __shared__ double part[LZ_MAX][1024 / WAVE];
-  __shared__ double h[LZ_MAX];
+  static_assert(KEEP % LS_B == 0, "whole batches");
+  constexpr int NW = LS_NT / WAVE;
+  __shared__ double part[2][LZ_MAX + LS_B][NW];
+  __shared__ double red[NW];
   const int tid = threadIdx.x, wave = tid / WAVE, lane = tid & (WAVE - 1);
-  if (j >= st->active) return;
   const int n4 = n_pad / 4;
   const float4* Q4 = reinterpret_cast<const float4*>(Q);
   float4* w4 = reinterpret_cast<float4*>(w);
-  int idx[LS_CH];
-  bool ok[LS_CH];
-  float4 wr[LS_CH], qj[LS_CH], qp[LS_CH];
-  const double bprev = j > 0 ? st->beta[j - 1] : 0.0;
+  int idx[CH];
+  bool ok[CH];
+  float4 wr[CH], qk[KEEP][CH];
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c) {
-    idx[c] = tid + 1024 * c;
+  for (int c = 0; c < CH; ++c) {
+    idx[c] = tid + LS_NT * c;
     ok[c] = idx[c] < n4;
     wr[c] = ld4_or0(w4, idx[c], ok[c]);
-    qj[c] = ld4_or0(Q4, (long long)j * n4 + idx[c], ok[c]);
-    qp[c] = ld4_or0(Q4, (long long)(j > 0 ? j - 1 : 0) * n4 + idx[c], ok[c] && j > 0);
   }
-  double acc = 0.0;
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c) acc += dot4(qj[c], wr[c]);
-  const double a = block_sum(acc, red);
+  for (int v0 = 0; v0 < KEEP; v0 += LS_B) {
+    if (v0 > j) break;   // uniform
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c) {
-    wr[c].x = (float)((double)wr[c].x - a * qj[c].x - (j > 0 ? bprev * qp[c].x : 0.0));
-    wr[c].y = (float)((double)wr[c].y - a * qj[c].y - (j > 0 ? bprev * qp[c].y : 0.0));
-    wr[c].z = (float)((double)wr[c].z - a * qj[c].z - (j > 0 ? bprev * qp[c].z : 0.0));
-    wr[c].w = (float)((double)wr[c].w - a * qj[c].w - (j > 0 ? bprev * qp[c].w : 0.0));
+    for (int u = 0; u < LS_B; ++u)
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        qk[v0 + u][c] = ld4_or0(Q4, (long long)(v0 + u) * n4 + idx[c], v0 + u <= j && ok[c]);
   }
+  if (j >= st->active) return;
+  double a = 0.0;
+#pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
-    for (int v0 = 0; v0 <= j; v0 += LS_B) {
-      float4 qa[LS_B][LS_CH];
+    const auto dots = [&](int v0, const float4 (&q)[LS_B][CH]) {   // (vectors past j read as zeros)
+      double d[LS_B];
+#pragma unroll
+      for (int u = 0; u < LS_B; ++u) {
+        d[u] = 0.0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) d[u] += dot4(q[u][c], wr[c]);
+      }
+      const double y = wave_sum4(d);
+      if ((lane & 15) == 0) part[pass][v0 + (lane >> 4)][wave] = y;
+    };
+    const auto batch = [&](int v0, float4 (&q)[LS_B][CH]) {
 #pragma unroll
       for (int u = 0; u < LS_B; ++u)
 #pragma unroll
-        for (int c = 0; c < LS_CH; ++c)
-          qa[u][c] = ld4_or0(Q4, (long long)(v0 + u) * n4 + idx[c], v0 + u <= j && ok[c]);
+        for (int c = 0; c < CH; ++c) q[u][c] = ld4_or0(Q4, (long long)(v0 + u) * n4 + idx[c], v0 + u <= j && ok[c]);
+    };
 #pragma unroll
-      for (int u = 0; u < LS_B; ++u) {
-        if (v0 + u <= j) {   // uniform over the work-group
-          double d = 0.0;
-#pragma unroll
-          for (int c = 0; c < LS_CH; ++c) d += dot4(qa[u][c], wr[c]);
-          d = wave_sum(d);
-          if (lane == 0) part[v0 + u][wave] = d;
-        }
-      }
+    for (int v0 = 0; v0 < KEEP; v0 += LS_B) {
+      if (v0 > j) break;
+      const float4(&q)[LS_B][CH] = *reinterpret_cast<const float4(*)[LS_B][CH]>(&qk[v0]);
+      dots(v0, q);
+    }
+    for (int v0 = KEEP; v0 <= j; v0 += LS_B) {
+      float4 q[LS_B][CH];
+      batch(v0, q);
+      dots(v0, q);
     }
     __syncthreads();
-    if (tid <= j) {
-      double t = 0.0;
-      for (int q = 0; q < 1024 / WAVE; ++q) t += part[tid][q];
-      h[tid] = t;
-    }
-    __syncthreads();
-    double t[LS_CH][4];
+    double hl = 0.0;   // lane v: h_v (v <= j < LZ_MAX = 64)
+    if (lane <= j) {
 #pragma unroll
-    for (int c = 0; c < LS_CH; ++c) {
+      for (int q = 0; q < NW; ++q) hl += part[pass][lane][q];
+    }
+    if (pass == 0) a = lane_value(hl, j);
+    double t[CH][4];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
       t[c][0] = wr[c].x;
       t[c][1] = wr[c].y;
       t[c][2] = wr[c].z;
       t[c][3] = wr[c].w;
     }
-    for (int v0 = 0; v0 <= j; v0 += LS_B) {
-      float4 qa[LS_B][LS_CH];
-#pragma unroll
-      for (int u = 0; u < LS_B; ++u)
-#pragma unroll
-        for (int c = 0; c < LS_CH; ++c)
-          qa[u][c] = ld4_or0(Q4, (long long)(v0 + u) * n4 + idx[c], v0 + u <= j && ok[c]);
+    const auto sub = [&](int v0, const float4 (&q)[LS_B][CH]) {
 #pragma unroll
       for (int u = 0; u < LS_B; ++u) {
-        if (v0 + u <= j) {
-          const double hv = h[v0 + u];
+        const double hv = lane_value(hl, min(v0 + u, j));
 #pragma unroll
-          for (int c = 0; c < LS_CH; ++c) {
-            t[c][0] -= hv * qa[u][c].x;
-            t[c][1] -= hv * qa[u][c].y;
-            t[c][2] -= hv * qa[u][c].z;
-            t[c][3] -= hv * qa[u][c].w;
-          }
+        for (int c = 0; c < CH; ++c) {   // (zeros past j)
+          t[c][0] -= hv * q[u][c].x;
+          t[c][1] -= hv * q[u][c].y;
+          t[c][2] -= hv * q[u][c].z;
+          t[c][3] -= hv * q[u][c].w;
         }
       }
+    };
+#pragma unroll
+    for (int v0 = 0; v0 < KEEP; v0 += LS_B) {
+      if (v0 > j) break;
+      const float4(&q)[LS_B][CH] = *reinterpret_cast<const float4(*)[LS_B][CH]>(&qk[v0]);
+      sub(v0, q);
+    }
+    for (int v0 = KEEP; v0 <= j; v0 += LS_B) {
+      float4 q[LS_B][CH];
+      batch(v0, q);
+      sub(v0, q);
     }
 #pragma unroll
-    for (int c = 0; c < LS_CH; ++c)
+    for (int c = 0; c < CH; ++c)
       wr[c] = make_float4((float)t[c][0], (float)t[c][1], (float)t[c][2], (float)t[c][3]);
-    __syncthreads();   // part and h are reused by the next pass
   }
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c)
+  for (int c = 0; c < CH; ++c)
     if (ok[c]) w4[idx[c]] = wr[c];
   if (tid == 0) {
     st->alpha[j] = a;
@@ -206,15 +239,21 @@ __global__ __launch_bounds__(1024) void lanczos_step_kernel(float* Q, int n_pad,
   if (j == m - 1) return;
   double nn = 0.0;
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c) nn += dot4(wr[c], wr[c]);
-  const double beta = sqrt(block_sum(nn, red));
+  for (int c = 0; c < CH; ++c) nn += dot4(wr[c], wr[c]);
+  nn = wave_sum(nn);
+  if (lane == 0) red[wave] = nn;
+  __syncthreads();
+  nn = 0.0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) nn += red[q];
+  const double beta = sqrt(nn);
   if (beta == 0.0) {
     if (tid == 0) st->active = j + 1;
     return;
   }
   float4* qn = reinterpret_cast<float4*>(Q + (long long)(j + 1) * n_pad);
 #pragma unroll
-  for (int c = 0; c < LS_CH; ++c)
+  for (int c = 0; c < CH; ++c)
     if (ok[c])
       qn[idx[c]] = make_float4((float)((double)wr[c].x / beta), (float)((double)wr[c].y / beta),
                                (float)((double)wr[c].z / beta), (float)((double)wr[c].w / beta));
@@ -236,7 +275,7 @@ __global__ __launch_bounds__(1024) void lanczos_step_kernel(float* Q, int n_pad,
 // returns at once.
 constexpr int LZ_BLOCK = 256;
 constexpr int LZ_MULTI_MIN = 8192;   // n_pad from which the step spreads over work-groups
-static_assert(LZ_MULTI_MIN / 4 <= LS_CH * 1024, "the one-work-group step holds n_pad / 4 chunks in LS_CH per thread");
+static_assert(LZ_MULTI_MIN / 4 <= 4 * 512, "the one-work-group step holds n_pad / 4 chunks in four per thread");
 
 __host__ __device__ inline int lanczos_partials(int n_pad) { return 4 * ((n_pad + LZ_BLOCK - 1) / LZ_BLOCK); }
 
@@ -652,7 +691,12 @@ static void lanczos(const PsdPlan& p, const float* R, uint64_t seed, float* thet
     hipLaunchKernelGGL(gemv_kernel, gg, gb, 0, st, R, np, np, p.qlan + (long long)j * np, p.t);
     hipLaunchKernelGGL(gemv_kernel, gg, gb, 0, st, R, np, np, p.t, p.w);
     if (np < LZ_MULTI_MIN) {
-      hipLaunchKernelGGL(lanczos_step_kernel, dim3(1), dim3(1024), 0, st, p.qlan, np, p.w, j, p.lz, p.lst);
+#define SD_LSTEP(NT, CH, KEEP)                                                                                   \
+  hipLaunchKernelGGL((lanczos_step_kernel<NT, CH, KEEP>), dim3(1), dim3(NT), 0, st, p.qlan, np, p.w, j, p.lz, p.lst)
+      if (np <= 2048) SD_LSTEP(512, 1, 20);
+      else if (np <= 4096) SD_LSTEP(512, 2, 12);
+      else SD_LSTEP(512, 4, 4);
+#undef SD_LSTEP
       continue;
     }
     const dim3 lg((np + LZ_BLOCK - 1) / LZ_BLOCK), lb(LZ_BLOCK);

@@ -20,6 +20,22 @@ def offset(a: np.ndarray) -> torch.Tensor:
     return t.copy_(torch.from_numpy(a))
 
 
+@pytest.mark.parametrize("n,steps", [(1, 20), (130, 4), (2048, 20), (2048, 25), (2049, 12), (2049, 13), (4096, 20),
+                                     (4097, 5), (8064, 20), (1000, 64), (3000, 64), (4200, 64)])
+def test_lanczos_steps(n, steps):
+    """Both ends of each length's variant, with fewer and more steps than the
+    basis vectors it keeps; theta (no deflation, no filter steps) against the
+    float64 recurrence of the oracle. The estimate is a converged Ritz value or
+    has a full-length recurrence behind it, so float32 storage of the basis
+    enters it squared: 1e-5 as for the longer steps."""
+    z = workloads.sym_gaussian(n, case_id=1)
+    say(f"lanczos n={n} steps={steps}")
+    out, info = sd.psd_project(torch.from_numpy(z).cuda(), 0, 0, None, lanczos_steps=steps, info=True)
+    z64 = z.astype(np.float64)
+    want = opsd.lanczos_scale(lambda x: z64 @ (z64 @ x), n, 0, steps)
+    assert abs(float(info["theta"]) - want) <= 1e-5 * want
+
+
 @pytest.mark.parametrize("n,k", [(1, 0), (2, 1), (63, 4), (64, 4), (65, 16), (130, 8), (131, 17), (132, 40), (1100, 32)])
 @pytest.mark.parametrize("aligned", [True, False])
 def test_output_tiles(n, k, aligned):
