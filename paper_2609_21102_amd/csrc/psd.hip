@@ -732,7 +732,6 @@ __global__ __launch_bounds__(WAVE) void frob_scale_kernel(const float* sumsq, in
 // ------------------------------------------- wide tracked bases ----------
 constexpr int BJ_MAX_SWEEPS = 16;   // block Jacobi sweep cap
 constexpr int BJ_TOL_EXP = -40;     // stop at off(H) <= 2^-40 ||H||_F
-constexpr int BJ_INNER_ROUNDS = BJ_P - 1;   // one sweep of the pair problem per round
 
 // C = A B^T over the panel rows (kp x kp, float64), SYM: A == B; part: the
 // chunk partials' scratch.
@@ -795,20 +794,25 @@ static void ritz_wide(const PsdPlan& p, const float* vt, const float* zt, const 
   ProfScope ps(SD_STAGE_SMALL, st);
   const int kp = p.kp, np = p.n_pad, nb = kp / BJ_B, P = nb / 2, rps = nb - 1;
   wide_products(p, vt, zt, false, p.wpart, p.g64, st);
-  hipLaunchKernelGGL(bj_init_kernel, dim3(cdiv(kp * kp, 256)), dim3(256), 0, st, p.g64, kp, p.hb0, p.eb0, p.bst);
-  const dim3 grid(P * P + P * (kp / BJ_P));
-  for (int sweep = 0; sweep < BJ_MAX_SWEEPS; ++sweep) {
-    for (int t = 0; t < rps; ++t) {
-      const long long g = (long long)sweep * rps + t;
-      const bool odd = g & 1;
-      const int flags = (t == rps - 1 ? BJ_WRITE_PART : 0) | (t == 0 && sweep > 0 ? BJ_TEST_PART : 0);
-      hipLaunchKernelGGL(bj_round_kernel, grid, dim3(128), 0, st, odd ? p.hb1 : p.hb0, odd ? p.hb0 : p.hb1,
-                         odd ? p.eb1 : p.eb0, odd ? p.eb0 : p.eb1, kp, nb, t, BJ_INNER_ROUNDS, sweep, flags,
-                         BJ_TOL_EXP, p.bjpart, p.bst);
+  if (p.K <= SM_MAX) {
+    hipLaunchKernelGGL(bj_one_kernel, dim3(1), dim3(1024), 0, st, p.g64, kp, p.K, p.hb0, p.eb0, p.bst,
+                       o.status_dev);
+  } else {
+    hipLaunchKernelGGL(bj_init_kernel, dim3(cdiv(kp * kp, 256)), dim3(256), 0, st, p.g64, kp, p.hb0, p.eb0, p.bst);
+    const dim3 grid(P * P + P * (kp / BJ_P));
+    for (int sweep = 0; sweep < BJ_MAX_SWEEPS; ++sweep) {
+      for (int t = 0; t < rps; ++t) {
+        const long long g = (long long)sweep * rps + t;
+        const bool odd = g & 1;
+        const int flags = (t == rps - 1 ? BJ_WRITE_PART : 0) | (t == 0 && sweep > 0 ? BJ_TEST_PART : 0);
+        hipLaunchKernelGGL(bj_round_kernel, grid, dim3(128), 0, st, odd ? p.hb1 : p.hb0, odd ? p.hb0 : p.hb1,
+                           odd ? p.eb1 : p.eb0, odd ? p.eb0 : p.eb1, kp, nb, t, sweep, flags, BJ_TOL_EXP, p.bjpart,
+                           p.bst);
+      }
     }
+    hipLaunchKernelGGL(bj_final_kernel, dim3(1), dim3(128), 0, st, p.bjpart, P * P, BJ_MAX_SWEEPS, BJ_TOL_EXP, p.bst,
+                       o.status_dev);
   }
-  hipLaunchKernelGGL(bj_final_kernel, dim3(1), dim3(128), 0, st, p.bjpart, P * P, BJ_MAX_SWEEPS, BJ_TOL_EXP, p.bst,
-                     o.status_dev);
   hipLaunchKernelGGL(ritz_wide_kernel, dim3(1), dim3(1024), 0, st, p.hb0, p.hb1, p.eb0, p.eb1, rps, p.bst, p.K, kp,
                      o.tau, o.window, o.gamma, p.e64, p.lam, p.ndef, p.coefR, p.coefX, p.coefP, o.ritz_out,
                      o.n_deflated_out, o.n_positive_out);

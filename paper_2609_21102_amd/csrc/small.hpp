@@ -259,6 +259,78 @@ __device__ __forceinline__ int jacobi_eig_wave(S& s, int n, int tol_exp, int max
   return R;
 }
 
+// One pass over the pairs between two halves of the indices, on one wave: NP
+// rounds that rotate the pairs (p, NP + (p + r) % NP), r = 0 .. NP - 1, of the
+// 2 NP x 2 NP matrix in s.h (lanes, blocks, angles and skip rule as in
+// jacobi_eig_wave; the T slots stay, the B slots move one step per round and
+// are back in place at the end). s.e is the accumulated rotation. The skip
+// threshold is relative to the norm of the matrix.
+template <int NP, typename S>
+__device__ __forceinline__ void jacobi_cross_wave(S& s, int tol_exp) {
+  static_assert(NP * NP <= WAVE, "one 2 x 2 block per lane");
+  const int lane = (int)(threadIdx.x & (WAVE - 1));
+  const bool act = lane < NP * NP;
+  const int bp = act ? lane / NP : 0, bq = act ? lane - bp * NP : 0;
+  const int np = (bp + 1) % NP, nq = (bq + 1) % NP;   // the next round's B partners
+  double h[4], e[4], tp[3], tq[3], fro = 0.0;
+#pragma unroll
+  for (int r1 = 0; r1 < 2; ++r1)
+#pragma unroll
+    for (int r2 = 0; r2 < 2; ++r2) {
+      const int a = jw_slot<NP>(r1, bp), b = jw_slot<NP>(r2, bq);
+      const double v = act ? s.h[a][b] : 0.0;
+      h[2 * r1 + r2] = v;
+      fro += v * v;
+      e[2 * r1 + r2] = (act && 2 * bp + r1 == b) ? 1.0 : 0.0;
+    }
+  tp[0] = s.h[bp][bp];
+  tp[1] = s.h[NP + bp][NP + bp];
+  tp[2] = s.h[bp][NP + bp];
+  tq[0] = s.h[bq][bq];
+  tq[1] = s.h[NP + bq][NP + bq];
+  tq[2] = s.h[bq][NP + bq];
+  fro = wave_sum(fro);
+  const double abs_floor = __builtin_amdgcn_ldexp(sqrt(fro), tol_exp);
+  for (int R = 0; R < NP; ++R) {
+    float cf = 1.f, tf = 0.f, cg = 1.f, tg = 0.f;
+    if (jacobi_rotates(tp[0], tp[1], tp[2], abs_floor)) jacobi_angle_f(tp[0], tp[1], tp[2], cf, tf);
+    if (jacobi_rotates(tq[0], tq[1], tq[2], abs_floor)) jacobi_angle_f(tq[0], tq[1], tq[2], cg, tg);
+    double cp, sp, cq, sq;
+    jacobi_rot64(cf, tf, cp, sp);
+    jacobi_rot64(cg, tg, cq, sq);
+    jacobi_apply(h, e, cp, sp, cq, sq);
+    if (act) {
+      s.h2[bp][bq] = h[0];
+      s.h2[bp][NP + bq] = h[1];
+      s.h2[NP + bp][bq] = h[2];
+      s.h2[NP + bp][NP + bq] = h[3];
+      s.e2[2 * bp][NP + bq] = e[1];
+      s.e2[2 * bp + 1][NP + bq] = e[3];
+    }
+    wave_sync();
+    if (act) {
+      h[1] = s.h2[bp][NP + nq];
+      h[2] = s.h2[NP + np][bq];
+      h[3] = s.h2[NP + np][NP + nq];
+      e[1] = s.e2[2 * bp][NP + nq];
+      e[3] = s.e2[2 * bp + 1][NP + nq];
+      tp[0] = s.h2[bp][bp];
+      tp[1] = s.h2[NP + np][NP + np];
+      tp[2] = s.h2[bp][NP + np];
+      tq[0] = s.h2[bq][bq];
+      tq[1] = s.h2[NP + nq][NP + nq];
+      tq[2] = s.h2[bq][NP + nq];
+    }
+    wave_sync();
+  }
+  if (act)
+#pragma unroll
+    for (int r1 = 0; r1 < 2; ++r1)
+#pragma unroll
+      for (int r2 = 0; r2 < 2; ++r2) s.e[2 * bp + r1][jw_slot<NP>(r2, bq)] = e[2 * r1 + r2];
+  wave_sync();
+}
+
 // ---------------------------------------------------- work-group Jacobi ----
 // The same scheme and the same values for 16 < n <= 2 NP <= 64 on a whole
 // work-group of NT threads, one 2 x 2 block per thread (NP = 12, 16: 256
@@ -270,9 +342,10 @@ __device__ __forceinline__ int jacobi_eig_wave(S& s, int n, int tol_exp, int max
 // registers, and passes (c, s) to the others through LDS. Two barriers per
 // round: after the angles (which also publishes that a pair rotates, and the
 // diagonal for the idle test), and after the ring step's writes. Skipped pairs
-// get (1, 0), which leaves values as they are.
+// get (1, 0), which leaves values as they are. True when it ended because no
+// entry of a finite matrix was left to rotate.
 template <int NP, int NT>
-__device__ __forceinline__ void jacobi_eig_group(SmallLds& s, int n, int tol_exp) {
+__device__ __forceinline__ bool jacobi_eig_group(SmallLds& s, int n, int tol_exp) {
   constexpr int N = 2 * NP, NB = NP * NP;
   static_assert(N <= SM_MAX && NB <= NT, "one 2 x 2 block per thread");
   const int t = (int)threadIdx.x;
@@ -294,7 +367,8 @@ __device__ __forceinline__ void jacobi_eig_group(SmallLds& s, int n, int tol_exp
   fro = block_sum(fro, s.red);
   const double abs_floor = __builtin_amdgcn_ldexp(sqrt(fro), tol_exp);
   int idle = 0, R = 0;
-  while (idle < N - 1 && R < 40 * (N - 1)) {
+  bool conv = false;
+  while (!conv && R < 40 * (N - 1)) {
     if (diag) {
       double c = 1.0, sn = 0.0;
       if (jacobi_rotates(h[0], h[3], h[1], abs_floor)) {
@@ -312,7 +386,7 @@ __device__ __forceinline__ void jacobi_eig_group(SmallLds& s, int n, int tol_exp
       jacobi_apply(h, e, rp[0], rp[1], rq[0], rq[1]);
     } else {
       // idle round: stop when the rule fires on no entry (jacobi_eig_wave)
-      ++idle;
+      conv = ++idle >= N - 1;
       bool any = false;
 #pragma unroll
       for (int r1 = 0; r1 < 2; ++r1)
@@ -320,7 +394,10 @@ __device__ __forceinline__ void jacobi_eig_group(SmallLds& s, int n, int tol_exp
         for (int r2 = 0; r2 < 2; ++r2)
           any |= act && (bp != bq || r1 != r2) &&
                  jacobi_rotates(s.key[jw_slot<NP>(r1, bp)], s.key[jw_slot<NP>(r2, bq)], h[2 * r1 + r2], abs_floor);
-      if (!__syncthreads_or(any)) break;
+      if (!__syncthreads_or(any)) {
+        conv = true;
+        break;
+      }
     }
     if (act)
 #pragma unroll
@@ -355,6 +432,7 @@ __device__ __forceinline__ void jacobi_eig_group(SmallLds& s, int n, int tol_exp
       }
     }
   __syncthreads();
+  return conv && fro < __builtin_inf();
 }
 
 // Threads of a work-group that solves an eigenproblem of class NP.

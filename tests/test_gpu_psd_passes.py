@@ -36,6 +36,29 @@ def test_lanczos_steps(n, steps):
     assert abs(float(info["theta"]) - want) <= 1e-5 * want
 
 
+@pytest.mark.parametrize("k", [33, 48, 63, 64, 65])
+def test_wide_ritz_widths(k):
+    """One work-group up to K = 64, block Jacobi from 65."""
+    case = workloads.small_psd(260, k=k, n_dom=k // 2, case_id=44)
+    z, q = torch.from_numpy(case.z).cuda(), torch.from_numpy(case.qwarm).cuda()
+    out, info = sd.psd_project(z, k, case.steps, q, subspace_iters=2, gamma=case.gamma, info=True)
+    want, basis, oinfo = opsd.psd_project_deflated(case.z.astype(np.float64), case.qwarm.astype(np.float64),
+                                                   steps=case.steps, gamma=case.gamma, subspace_iters=2)
+    assert int(info["status"]) == 0
+    assert rel_fro(host64(out), want) < 1e-4 and rel_fro(host64(q), basis) < 1e-4
+    np.testing.assert_allclose(info["ritz"].cpu().numpy(), oinfo.ritz, rtol=1e-4, atol=1e-5 * abs(oinfo.ritz[0]))
+
+
+@pytest.mark.parametrize("k", [40, 70])
+def test_wide_ritz_flags_nan(k):
+    """An eigenproblem that cannot converge sets the flag on both routes."""
+    case = workloads.small_psd(200, k=k, case_id=45)
+    z = case.z.copy()
+    z[3, 5] = z[5, 3] = np.nan
+    _, info = sd.psd_project(torch.from_numpy(z).cuda(), k, 5, torch.from_numpy(case.qwarm).cuda(), info=True)
+    assert int(info["status"]) & 8
+
+
 @pytest.mark.parametrize("n,k", [(1, 0), (2, 1), (63, 4), (64, 4), (65, 16), (130, 8), (131, 17), (132, 40), (1100, 32)])
 @pytest.mark.parametrize("aligned", [True, False])
 def test_output_tiles(n, k, aligned):
