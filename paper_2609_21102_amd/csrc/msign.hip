@@ -307,7 +307,7 @@ static int run_msign(const MsignPlan& p, const float* coeffs, const sd_msign_opt
   int ldx;
   if (p.copy_in) {
     T* dst = reinterpret_cast<T*>(p.xc);
-    const int blocks = (p.s_pad / 32) * (p.l_pad / 32) * B;
+    const int blocks = (p.s_pad / CC_TILE) * (p.l_pad / CC_TILE) * B;
     hipLaunchKernelGGL((canon_copy_kernel<T>), dim3(blocks), dim3(256), 0, st, dst, sl, p.l_pad, p.s_pad,
                        p.l_pad, in, (long long)p.m * p.n, p.s, p.l, p.tall ? 1 : 0, B);
     xc = dst;

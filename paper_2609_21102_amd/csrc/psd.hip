@@ -854,7 +854,7 @@ static int run_psd(const PsdPlan& p, const float* X, float* Qwarm, float* out, c
   const long long nn = (long long)np * np;
   const float* z;
   if (p.copy_in) {
-    const int blocks = (np / 32) * (np / 32);
+    const int blocks = (np / CC_TILE) * (np / CC_TILE);
     hipLaunchKernelGGL((canon_copy_kernel<float>), dim3(blocks), dim3(256), 0, st, p.zp, nn, np, np, np, X, nn, n,
                        n, 0, 1);
     z = p.zp;

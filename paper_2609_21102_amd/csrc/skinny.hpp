@@ -325,39 +325,63 @@ static __global__ void sketch_copy_kernel(float* __restrict__ Wt, long long sw, 
 }
 
 // ----------------------------------------------------- canonical copy ----
-// dst[b][i][n] (padded rows_pad x ld, zero outside rows x cols) from
-// src[b] of shape rows x cols (row-major) or, with transpose, cols x rows.
+// dst[b][i][n] (padded rows_pad x ld, multiples of 64 and 16-byte aligned; zero
+// outside rows x cols) from src[b] of shape rows x cols (row-major) or, with
+// transpose, cols x rows. Bound by memory: a work-group moves one 64 x 64 tile
+// of dst in 16-byte stores, and in 16-byte loads where src's pitch and address
+// allow; all of a thread's loads come before its stores (9 x 5120 x 1280 bf16
+// 120 -> 39 us, 6.1 TB/s, from 32 x 32 tiles with one element per access).
+constexpr int CC_TILE = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void canon_copy_kernel(T* __restrict__ dst, long long sd_, int ldd, int rows_pad,
                                                          int cols_pad, const T* __restrict__ src, long long ss,
                                                          int rows, int cols, int transpose, int batch) {
-  __shared__ T tile[32][33];
-  const int tr = rows_pad / 32, tc = cols_pad / 32;
+  constexpr int V = 16 / (int)sizeof(T), CH = CC_TILE / V, PER = CC_TILE * CH / 256;   // V elements per access
+  __shared__ __attribute__((aligned(16))) T tile[CC_TILE][CC_TILE + 4 / sizeof(T)];
+  typedef T vec_t __attribute__((ext_vector_type(V)));
+  const int tr = rows_pad / CC_TILE, tc = cols_pad / CC_TILE;
   const int per = tr * tc;
   const int b = blockIdx.x / per;
   if (b >= batch) return;
   const int t = blockIdx.x - b * per;
-  const int r0 = (t / tc) * 32, c0 = (t % tc) * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
+  const int r0 = (t / tc) * CC_TILE, c0 = (t % tc) * CC_TILE;
+  const int tid = threadIdx.x;
   const T* sb = src + b * ss;
   T* db = dst + b * sd_;
-  if (!transpose) {
-    for (int y = ty; y < 32; y += 8) {
-      const int r = r0 + y, c = c0 + tx;
-      T v = T(0);
-      if (r < rows && c < cols) v = sb[(long long)r * cols + c];
-      db[(long long)r * ldd + c] = v;
+  // the source tile: srows x scols from (sr0, sc0)
+  const int srows = transpose ? cols : rows, scols = transpose ? rows : cols;
+  const int sr0 = transpose ? c0 : r0, sc0 = transpose ? r0 : c0;
+  const bool vs = scols % V == 0 && reinterpret_cast<uintptr_t>(sb) % 16 == 0;
+  vec_t v[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = tid + 256 * u, r = sr0 + e / CH, c = sc0 + V * (e % CH);
+    const T* p = sb + (long long)r * scols + c;
+    if (vs && r < srows && c < scols) {
+      v[u] = *reinterpret_cast<const vec_t*>(p);
+    } else {
+#pragma unroll
+      for (int q = 0; q < V; ++q) v[u][q] = r < srows && c + q < scols ? p[q] : T(0);
     }
-  } else {
-    // dst(r, c) = src(c, r); src is cols x rows.
-    for (int y = ty; y < 32; y += 8) {
-      const int sr = c0 + y, sc = r0 + tx;
-      T v = T(0);
-      if (sr < cols && sc < rows) v = sb[(long long)sr * rows + sc];
-      tile[y][tx] = v;
+  }
+  if (transpose) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + 256 * u, r = e / CH, c = V * (e % CH);
+#pragma unroll
+      for (int q = 0; q < V; ++q) tile[c + q][r] = v[u][q];
     }
     __syncthreads();
-    for (int y = ty; y < 32; y += 8) db[(long long)(r0 + y) * ldd + c0 + tx] = tile[tx][y];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + 256 * u;
+      __builtin_memcpy(&v[u], __builtin_assume_aligned(&tile[e / CH][V * (e % CH)], 4), 16);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = tid + 256 * u;
+    *reinterpret_cast<vec_t*>(db + (long long)(r0 + e / CH) * ldd + c0 + V * (e % CH)) = v[u];
   }
 }
 
