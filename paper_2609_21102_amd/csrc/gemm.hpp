@@ -464,6 +464,7 @@ struct EpiUpdateHL {
   static constexpr bool PRE = true;
   static constexpr bool ROWWISE = true;
   static constexpr bool HI_FROM_B = true;
+  static constexpr bool TRANSPOSED = true;
   const T16* hi;
   const int8_t* lo;    // residual bytes, same element layout as hi
   long long xstride;
@@ -485,7 +486,7 @@ struct EpiUpdateHL {
     l = u32x4_t{w[0], w[1], 0u, 0u};
   }
   __device__ void apply8(int b, int r, int c0, const float (&acc)[8], const u32x4_t& h, const u32x4_t& l,
-                         float (&)[8]) const {
+                         float (&w)[8]) const {
     const uint32_t hw[4] = {h[0], h[1], h[2], h[3]};
     float v[8];
     if constexpr (HALF) hstate_value8(hw, l[0], l[1], v);
@@ -502,28 +503,43 @@ struct EpiUpdateHL {
       else st8_nt(out_lo + o, state_pack8(v, nh));
       return;
     }
-    if (r >= rows_valid) return;
     if constexpr (HALF) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] *= 1.f / HSTATE;
     }
-    TO* ob = out + b * ostride;
-    if (!transpose_out) {
-      if constexpr (sizeof(TO) == 2) {
-        if (c0 + 8 <= cols_valid && (ldo & 7) == 0) {
-          st16_nt(ob + (long long)r * ldo + c0,
-               u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])});
-          return;
-        }
-      }
+    if (transpose_out) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (c0 + q < cols_valid) ob[(long long)r * ldo + c0 + q] = Cvt<TO>::from_f(v[q]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (c0 + q < cols_valid) ob[(long long)(c0 + q) * ldo + r] = Cvt<TO>::from_f(v[q]);
+      for (int q = 0; q < 8; ++q) w[q] = v[q];
+      return;
     }
+    if (r >= rows_valid) return;
+    TO* ob = out + b * ostride;
+    if constexpr (sizeof(TO) == 2) {
+      if (c0 + 8 <= cols_valid && (ldo & 7) == 0) {
+        st16_nt(ob + (long long)r * ldo + c0,
+             u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])});
+        return;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (c0 + q < cols_valid) ob[(long long)r * ldo + c0 + q] = Cvt<TO>::from_f(v[q]);
+  }
+  // Tall inputs' last update: rows r8 .. r8 + 7 of column c, through LDS (9 x
+  // 5120 x 1280: 230 to 250 us; 325 with single elements stored from the row form).
+  __device__ bool transposed() const { return final_out && transpose_out; }
+  __device__ void store_t8(int b, int c, int r8, const float (&v)[8]) const {
+    if (c >= cols_valid) return;
+    TO* o = out + b * ostride + (long long)c * ldo + r8;
+    if constexpr (sizeof(TO) == 2) {
+      if (r8 + 8 <= rows_valid && reinterpret_cast<uintptr_t>(o) % 16 == 0) {
+        st16_nt(o, u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])});
+        return;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (r8 + q < rows_valid) o[q] = Cvt<TO>::from_f(v[q]);
   }
 };
 
@@ -674,6 +690,18 @@ struct EpiMirror {
 template <typename E>
 struct EpiMirror<E, std::void_t<decltype(E::MIRROR)>> {
   static constexpr bool value = E::MIRROR;
+};
+
+// Row-wise epilogues whose output may be the transpose of the product declare
+// TRANSPOSED = true: where transposed() says so, apply8 only hands its values
+// back and store_t8 stores eight rows of one column.
+template <typename E, typename = void>
+struct EpiTransposed {
+  static constexpr bool value = false;
+};
+template <typename E>
+struct EpiTransposed<E, std::void_t<decltype(E::TRANSPOSED)>> {
+  static constexpr bool value = E::TRANSPOSED;
 };
 
 // ------------------------------------------------------- staging ----------
@@ -1211,6 +1239,13 @@ __device__ __forceinline__ void lds_dma16(const void* g, char* base) {
 }
 #pragma clang diagnostic pop
 
+// Columns of row r of the row-wise epilogue's C tile that is read transposed
+// sit at column ^ mirror_swz(r): the pitch is a multiple of 64 banks over eight
+// rows, so the 8 or 16 lanes that read a column at rows 8 i would meet one bank
+// (16-way at 128 x 128); this way a wave's lanes meet 64: polynomial at 24 x 768 x
+// 768 35.0 -> 31.2 us, the other s x s products 36.2 -> 32.0.
+__device__ __forceinline__ int mirror_swz(int r) { return (r & 56) | ((r & 64) >> 4); }
+
 template <int CH>
 __device__ __forceinline__ int rowform_slot(int r, int c) {
   static_assert(CH == 4 || CH == 8, "K row of 4 or 8 chunks");
@@ -1504,6 +1539,8 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, const T* 
     __syncthreads();
     const bool diag = SYM && tm == tn;
     float mv[RW_CH][8];   // values of the transposed copy (symmetric tilings)
+    bool tr = false;      // the output is the transpose (tall inputs' last update)
+    if constexpr (EpiTransposed<Epi>::value) tr = epi.transposed();
 #pragma unroll
     for (int u = 0; u < RW_CH; ++u) {
       const int e = threadIdx.x + Cfg::NT * u;
@@ -1524,17 +1561,45 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, const T* 
           if (c8 + q < r) av[q] = ct[(c8 + q) * RW_LD + r];
       }
       epi.apply8(b, m0 + r, n0 + c8, av, rw_h[u], rw_l[u], mv[u]);
+      if constexpr (EpiTransposed<Epi>::value) {
+        // back into this row of the C tile (mirror_swz): the row belongs to one
+        // wave, whose reads of it are done
+        if (tr) {
+          static_assert(WAVE % (BN / 8) == 0, "a row of chunks within a wave");
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          const int sw = mirror_swz(r);
+          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + (c8 ^ sw)) = f32x4_t{mv[u][0], mv[u][1], mv[u][2], mv[u][3]};
+          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + ((c8 + 4) ^ sw)) =
+              f32x4_t{mv[u][4], mv[u][5], mv[u][6], mv[u][7]};
+        }
+      }
+    }
+    if constexpr (EpiTransposed<Epi>::value) {
+      if (tr) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < RW_CH; ++u) {
+          const int e = threadIdx.x + Cfg::NT * u;
+          const int c = e / (BM / 8), r8 = 8 * (e % (BM / 8));
+          float av[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) av[q] = ct[(r8 + q) * RW_LD + (c ^ mirror_swz(r8))];
+          epi.store_t8(b, n0 + c, m0 + r8, av);
+        }
+      }
     }
     if constexpr (SYM) {
       if (!diag) {
-        // the values to mirror go back into the C tile, then out transposed
+        // the values to mirror go back into the C tile (mirror_swz), then out transposed
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < RW_CH; ++u) {
           const int e = threadIdx.x + Cfg::NT * u;
           const int r = e / (BN / 8), c8 = 8 * (e % (BN / 8));
-          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + c8) = f32x4_t{mv[u][0], mv[u][1], mv[u][2], mv[u][3]};
-          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + c8 + 4) = f32x4_t{mv[u][4], mv[u][5], mv[u][6], mv[u][7]};
+          const int sw = mirror_swz(r);
+          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + (c8 ^ sw)) = f32x4_t{mv[u][0], mv[u][1], mv[u][2], mv[u][3]};
+          *reinterpret_cast<f32x4_t*>(ct + r * RW_LD + ((c8 + 4) ^ sw)) =
+              f32x4_t{mv[u][4], mv[u][5], mv[u][6], mv[u][7]};
         }
         __syncthreads();
 #pragma unroll
@@ -1543,7 +1608,7 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, const T* 
           const int c = e / (BM / 8), r8 = 8 * (e % (BM / 8));
           float av[8];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) av[q] = ct[(r8 + q) * RW_LD + c];
+          for (int q = 0; q < 8; ++q) av[q] = ct[(r8 + q) * RW_LD + (c ^ mirror_swz(r8))];
           epi.store8(b, n0 + c, m0 + r8, av);
         }
       }
