@@ -21,8 +21,9 @@ Prints one JSON line:
   stages     every stage of the call from HIP events around each launch (a
              second pass of the same calls): the filter's Gram, polynomial and
              update against the MFMA peak, the sketch products, the rank-k
-             passes and the CholeskyQR panels against HBM, each with its
-             algorithmic work, and the whole-call fraction sum_stage
+             passes and the CholeskyQR panels against HBM, each with the
+             work of its launches (the grouped filter's fewer Grams and
+             updates counted as launched), and the whole-call fraction sum_stage
              max(flops / MFMA peak, bytes / HBM peak) / call time;
   cpu_baseline  the CPU oracle on a bounded sample, at all cores and at one
              thread.
@@ -45,6 +46,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0
+MFMA_SPLIT_PEAK_TFLOPS = MFMA_BF16_PEAK_TFLOPS / 3   # float32 products: three on fp16 halves
 HBM_PEAK_GBS = 8000.0
 
 
@@ -53,8 +55,8 @@ def log(*a):
 
 
 def ns_flops_per_matrix(s: int, l: int, steps: int) -> float:
-    """Algorithmic flops of the filter for one s x l matrix: per step the Gram
-    X X^T and A^2 counted once per symmetric entry, plus the 2 s^2 l update."""
+    """Algorithmic flops of the filter for one s x l matrix, step by step (the
+    grouped filter does fewer for the same result): per step the Gram X X^T and A^2 counted once per symmetric entry, plus the 2 s^2 l update."""
     return steps * (s * (s + 1) * (l + s) + 2.0 * s * s * l)
 
 
@@ -88,6 +90,18 @@ def stage_work(s: int, l: int, k: int, rp: int, power_iters: int, steps: int) ->
         "cholqr": (0.0, 2 * 4.0 * rp * ((1 + power_iters) * l + power_iters * s)),
         "small": (0.0, 0.0),
     }
+
+
+def launched_work(work: dict, steps: int, launches: dict) -> dict:
+    """`work` with the filter's stages priced by the launches of a call
+    (launches[stage] per call, each the product of one step of stage_work): the
+    grouped filter runs fewer Grams and updates and more s x s products than
+    one of each per step."""
+    out = dict(work)
+    for name in ("ns_gram", "ns_poly", "ns_update"):
+        if name in launches and steps:
+            out[name] = tuple(w / steps * launches[name] for w in work[name])
+    return out
 
 
 STAGE_PEAKS = {"mfma_bf16_tflops": 2500.0, "hbm_gbs": 8000.0}
@@ -291,9 +305,9 @@ def _psd_update_roofline(sd, step, steps: int, n: int, precision: str) -> dict:
     flops = float(n_pad) * (n_pad + 1) * n_pad
     avg_ms = ms / max(launches, 1)
     tf = flops / (avg_ms / 1e3) / 1e12
-    peak = 157.3 if precision == "f32" else MFMA_BF16_PEAK_TFLOPS   # fp16 dense = bf16 dense
+    peak = MFMA_SPLIT_PEAK_TFLOPS if precision == "f32" else MFMA_BF16_PEAK_TFLOPS   # fp16 dense = bf16 dense
     return {"bound": "mfma", "kernel": "filter update X <- a X + X B, symmetric tiles "
-            + ("(gemm_dma_kernel, fp16 operands)" if precision == "f16" else "(gemm_kernel, fp32)"),
+            + ("(gemm_dma_kernel, fp16 operands)" if precision == "f16" else "(gemm_kernel, split fp32)"),
             "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak, "traffic": None,
             "flops_per_launch": flops, "avg_launch_us": avg_ms * 1e3, "launches": launches}
 
@@ -389,10 +403,12 @@ def other_workload(args) -> int:
         # bf16 MFMA peak
         upd_ms, upd_n = _stage_time(sd, step, args.steps, "ns_update")
         upd_bytes = upd_flops = 0.0
-        for c in cases:
+        for c, g in zip(cases, groups):
             b_, s_, l_ = c.x.shape[0], min(c.x.shape[1:]), max(c.x.shape[1:])
-            upd_bytes += b_ * update_bytes_algorithmic(s_, l_) * c.steps * args.steps
-            upd_flops += b_ * 2.0 * s_ * s_ * l_ * c.steps * args.steps
+            # updates of one call (groups of steps share one)
+            updates = _stage_time(sd, lambda: sd.msign_groups([g]), 1, "ns_update")[1]
+            upd_bytes += b_ * update_bytes_algorithmic(s_, l_) * updates * args.steps
+            upd_flops += b_ * 2.0 * s_ * s_ * l_ * updates * args.steps
         ach = upd_flops / (upd_ms / 1e3) / 1e12
         roof = {"bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach / MFMA_BF16_PEAK_TFLOPS, "flops_per_launch": upd_flops / max(upd_n, 1),
@@ -495,8 +511,9 @@ def other_workload(args) -> int:
                "steps": args.steps, "warmup": args.warmup, "dtype": "f32", "data": "synthetic",
                "config": {"workload": "c1", "m": 256, "n": 256, "k": case.k, "power_iters": case.power_iters,
                           "filter_steps": case.steps},
-               "roofline": {"bound": "mfma", "kernel": "iterate update X <- a X + B X (gemm_kernel, fp32)",
-                            "achieved": ach, "peak": 157.3, "unit": "TFLOP/s", "frac": ach / 157.3,
+               "roofline": {"bound": "mfma", "kernel": "iterate update X <- a X + B X (gemm_kernel, split fp32)",
+                            "achieved": ach, "peak": MFMA_SPLIT_PEAK_TFLOPS, "unit": "TFLOP/s",
+                            "frac": ach / MFMA_SPLIT_PEAK_TFLOPS,
                             "traffic": None, "avg_launch_us": upd_ms * 1e3 / max(upd_n, 1), "launches": upd_n,
                             "flops_per_launch": fl}}
     elif args.workload == "admm":
@@ -534,7 +551,7 @@ def other_workload(args) -> int:
                                  t_n / (args.steps * chunk)}
         # per step: X^2 and the update (n^3 each, symmetric), plus A^2 for a quintic
         flops = chunk * ((2.0 if degree == 3 else 3.0) * n ** 3 * steps + 2.0 * n ** 3)
-        peak = 157.3 if args.precision == "f32" else MFMA_BF16_PEAK_TFLOPS
+        peak = MFMA_SPLIT_PEAK_TFLOPS if args.precision == "f32" else MFMA_BF16_PEAK_TFLOPS
         res = {"metric": f"ADMM iterations/s (max-cut SDP, n = {n}, K = {k}, {steps} degree-{degree} steps, "
                          f"{args.precision} filter products)",
                "value": chunk * 1e3 / ms, "unit": "iterations/s", "ms_per_step": ms,
@@ -573,7 +590,7 @@ def other_workload(args) -> int:
         # cubic filter: X^2 and X X^2 are both symmetric and computed on upper-triangle
         # tiles (n^3 each per step), a quintic adds A^2; the restore product R g is a full 2 n^3
         flops = (2.0 if degree == 3 else 3.0) * n ** 3 * steps + 2.0 * n ** 3
-        peak = 157.3 if args.precision == "f32" else MFMA_BF16_PEAK_TFLOPS   # fp16 dense = bf16 dense
+        peak = MFMA_SPLIT_PEAK_TFLOPS if args.precision == "f32" else MFMA_BF16_PEAK_TFLOPS   # fp16 dense = bf16 dense
         res = {"metric": f"deflated PSD projections/s ({args.workload}: n = {n}, k = {k}, {steps} degree-{degree} "
                          f"steps, {args.precision} filter products)",
                "value": 1e3 / ms, "unit": "projections/s", "ms_per_step": ms,
@@ -681,12 +698,8 @@ def main() -> int:
     ms_per_step = ms_total / args.steps
     value = b * args.steps / (ms_total / 1e3)
     work = stage_work(s, l, k, rp, case.power_iters, case.steps)
-    flops = b * sum(w[0] for w in work.values()) if k else b * (work["ns_gram"][0] + work["ns_poly"][0] +
-                                                                 work["ns_update"][0])
-    tflops = flops / (ms_per_step / 1e3) / 1e12
     n_launch = max(upd_n, 1)
-    upd_flops = b * work["ns_update"][0] * args.steps / n_launch
-    upd_alg_bytes = b * work["ns_update"][1] * args.steps / n_launch
+    upd_flops, upd_alg_bytes = (b * w / max(case.steps, 1) for w in work["ns_update"])   # one update
     upd_avg_ms = upd_ms / n_launch
     upd_tflops = upd_flops / (upd_avg_ms / 1e3) / 1e12
 
@@ -699,6 +712,10 @@ def main() -> int:
     torch.cuda.synchronize()
     sd.profile_set()
     times = {nm: sd.profile_read(nm) for nm in names}
+    work = launched_work(work, case.steps, {nm: row[1] / args.steps for nm, row in times.items()})
+    flops = b * sum(w[0] for w in work.values()) if k else b * (work["ns_gram"][0] + work["ns_poly"][0] +
+                                                                 work["ns_update"][0])
+    tflops = flops / (ms_per_step / 1e3) / 1e12
     table = stage_table(times, work, b, args.steps, ms_per_step)
     log(f"bench: {ms_per_step:.3f} ms/step, {value:.0f} matrices/s, {tflops:.1f} TFLOP/s; "
         f"update {upd_avg_ms * 1e3:.1f} us avg over {upd_n} launches ({upd_tflops:.1f} TFLOP/s, "

@@ -228,19 +228,21 @@ static void filter_half(const MsignPlan& p, Coef coef, const SplitScales& sc, bf
     const f16_t* q = bm;   // Q_i - qa I, exponent eq
     int eq = f.eq[0];
     for (int i = 0; i < f.g; ++i) {
-      ProfScope ps(SD_STAGE_NS_POLY, st);
       const int t = f.t0 + i, eb = sc.b[t];
       coef(t, a, b, c);
       f16_t* const bi = i == 1 ? b1 : bm;
       if (f.g > 1 || c != 0.f) {   // B_i = b A_i + c A_i^2
+        ProfScope ps(SD_STAGE_NS_POLY, st);
         const EpiPoly<f16_t> e{p.a32, bi, b * pw(eb), c * pw(eb - 2 * ea), ss, p.s_pad};
         sym_gemm<f16_t>(a16, a16, gs, e, B16, st);
       }
       if (i + 1 < f.g) {           // W = P_i A_i
+        ProfScope ps(SD_STAGE_NS_POLY, st);
         const EpiPoly<f16_t> e{p.a32, w16, a * pw(ea), pw(-eb), ss, p.s_pad};
         sym_gemm<f16_t>(bi, a16, gs, e, B16, st);
       }
       if (i > 0) {                 // Q_i = P_i Q_{i-1}
+        ProfScope ps(SD_STAGE_NS_POLY, st);
         f16_t* const qn = i + 1 < f.g ? q1 : a16;
         const EpiLin16<> e{q, bi, pw(-eq - eb), a * pw(-eq), qa * pw(-eb), pw(f.eq[i]), nullptr, qn, ss, p.s_pad};
         sym_gemm<f16_t>(bi, q, gs, e, B16, st);
@@ -249,6 +251,7 @@ static void filter_half(const MsignPlan& p, Coef coef, const SplitScales& sc, bf
         qa *= a;
       }
       if (i + 1 < f.g) {           // A_{i+1} = W P_i
+        ProfScope ps(SD_STAGE_NS_POLY, st);
         const int en = sc.a[t + 1];
         const EpiLin16<> e{w16, nullptr, pw(-ea - eb), a * pw(-ea), 0.f, pw(en), p.a32, a16, ss, p.s_pad};
         sym_gemm<f16_t>(w16, bi, gs, e, 3 * B16, st);
